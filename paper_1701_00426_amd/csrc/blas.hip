@@ -18,7 +18,7 @@ namespace stg {
 // x += alpha p; r -= alpha q; block partials of |r|^2 (OP_BETA in the finalize kernel)
 template <typename T, int NR>
 __global__ __launch_bounds__(kBlock) void cg_update_kernel(VecArgs a) {
-    if (a.gate_running && a.ctl->n_running == 0) return;
+    if (gate_closed<NR>(a.state, a.gate_mask)) return;
     const uint32_t h = blockIdx.x * kBlock + threadIdx.x;
     double ps[NR], pc[NR];
 #pragma unroll
@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kBlock) void cg_update_kernel(VecArgs a) {
 // p = r + beta p
 template <typename T, int NR>
 __global__ __launch_bounds__(kBlock) void p_update_kernel(VecArgs a) {
-    if (a.gate_running && a.ctl->n_running == 0) return;
+    if (gate_closed<NR>(a.state, a.gate_mask)) return;
     const uint32_t h = blockIdx.x * kBlock + threadIdx.x;
     if (h >= a.Vh) return;
 #pragma unroll
@@ -90,7 +90,7 @@ __device__ __forceinline__ double block_total(const double *x, uint32_t n) {
 // next kernel turns into SYS_BREAKDOWN.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void cg_update_fused_kernel(VecArgs a) {
-    if (block_gate_closed(a.ctl, a.gate_running)) return;
+    if (block_gate_closed(a.ctl, a.gate_mask)) return;
     const double pq = block_total(a.fin_partials, a.fin_blocks);
     const SysState &s = a.state[0];
     const bool running = (s.flags & SYS_RUNNING) != 0;
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kBlock) void cg_update_fused_kernel(VecArgs a) {
 // always runs (also when no system runs), so that a.state_out is always current.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void p_update_fused_kernel(VecArgs a) {
-    const bool closed = block_gate_closed(a.ctl, a.gate_running);
+    const bool closed = block_gate_closed(a.ctl, a.gate_mask);
     if (closed && blockIdx.x != 0) return;
     SysState ns = a.state[0];
     ns.flags &= ~SYS_RESUME;
@@ -204,7 +204,7 @@ __device__ __forceinline__ double cgcg_site(const VecArgs &a, size_t o, uint32_t
 
 template <typename T, int NR>
 __global__ __launch_bounds__(kBlock) void cgcg_update_kernel(VecArgs a) {
-    if (a.gate_running && a.ctl->n_running == 0) return;
+    if (gate_closed<NR>(a.state, a.gate_mask)) return;
     const uint32_t h = blockIdx.x * kBlock + threadIdx.x;
     double ps[NR], pc[NR];
 #pragma unroll
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kBlock) void cgcg_update_kernel(VecArgs a) {
 // A breakdown or a system that parks leaves the vectors alone.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void cgcg_update_fused_kernel(VecArgs a) {
-    const bool closed = block_gate_closed(a.ctl, a.gate_running);
+    const bool closed = block_gate_closed(a.ctl, a.gate_mask);
     if (closed && blockIdx.x != 0) return;
     SysState ns = a.state[0];
     bool left = false, step = false;
@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kBlock) void ru_resume_kernel(VecArgs a) {
 // multi-shift (Sec. 2.2, Eq. shlineq): base residual r -= alpha q; |r|^2 -> OP_MS_BETA
 template <typename T, int NR>
 __global__ __launch_bounds__(kBlock) void ms_r_update_kernel(VecArgs a) {
-    if (a.gate_running && a.ctl->n_running == 0) return;
+    if (gate_closed<NR>(a.state, a.gate_mask)) return;
     const uint32_t h = blockIdx.x * kBlock + threadIdx.x;
     double ps[NR], pc[NR];
 #pragma unroll
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(kBlock) void ms_r_update_kernel(VecArgs a) {
 // stays in L2.
 template <typename T, int NR>
 __global__ __launch_bounds__(kBlock) void ms_p_update_kernel(VecArgs a) {
-    if (a.gate_running && a.ctl->n_running == 0) return;
+    if (gate_closed<NR>(a.state, a.gate_mask)) return;
     const uint32_t nk = (uint32_t)a.nshift + 1;
     const uint32_t lb = xcd_block(blockIdx.x, gridDim.x);
     const uint32_t k = lb % nk;
@@ -433,7 +433,7 @@ STG_VEC_LAUNCHER(launch_cgcg_update, cgcg_update_kernel)
 
 int launch_cg_update(const VecArgs &a, int fp64, int nr, hipStream_t stream) {
     if (launch_cg_update_only(a, fp64, nr, stream)) return -1;
-    FinArgs f{a.partials, site_blocks(a.Vh), nr, OP_BETA, a.gate_running, a.ctl, a.state, nullptr};
+    FinArgs f{a.partials, site_blocks(a.Vh), nr, OP_BETA, a.gate_mask, a.ctl, a.state, nullptr};
     return launch_finalize(f, stream);
 }
 
@@ -457,7 +457,7 @@ int launch_ms_p_update(const VecArgs &a, int fp64, int nr, hipStream_t stream) {
 
 int launch_ms_r_update(const VecArgs &a, int fp64, int nr, hipStream_t stream) {
     if (launch_ms_r_update_only(a, fp64, nr, stream)) return -1;
-    FinArgs f{a.partials, site_blocks(a.Vh), nr, OP_MS_BETA, a.gate_running, a.ctl, a.state,
+    FinArgs f{a.partials, site_blocks(a.Vh), nr, OP_MS_BETA, a.gate_mask, a.ctl, a.state,
               nullptr};
     return launch_finalize(f, stream);
 }
@@ -467,8 +467,10 @@ int launch_ms_r_update(const VecArgs &a, int fp64, int nr, hipStream_t stream) {
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void finalize_kernel(FinArgs f) {
     __shared__ double sh_red[2 * kWaves];
-    if (block_gate_closed(f.ctl, f.gate_running)) return;
     const int j = blockIdx.x;
+    // every thread reads its block's own system before the first barrier of the sum;
+    // thread 0 changes it only after the last one
+    if (f.gate_mask && !(f.state[j].flags & f.gate_mask)) return;
     double tot = block_sum2_pairs(f.partials + 2 * (size_t)j * f.nblocks, (int)f.nblocks, sh_red);
     double tot2 = 0.0;
     if (f.op == OP_CGCG)

@@ -333,6 +333,7 @@ struct CgProblem {
     int group = 0;     // systems s share b[s % group] (multi-shift refinement); 0: group = nsys
     int cap = 8;       // fields per launch (field_cap of the inner links)
     bool cgcg = false; // the single-reduction form of the iteration
+    // fields of the true-residual update's launch from system j0 on: contiguous in b too
     int chunk(int j0) const {
         const int g = group > 0 ? group : nsys;
         return chunk_of(std::min(nsys - j0, g - j0 % g), cap);
@@ -343,10 +344,35 @@ struct CgProblem {
     }
 };
 
-// One CG iteration for every chunk of systems that still has a running system in
-// the flags snapshot `st` (systems leave the running state only inside the
-// iteration, and re-enter it only through a reliable update, after which the host
-// reads fresh flags: a snapshot one chunk old never skips a running system).
+// The launches of one CG iteration: the systems that have not finished, in chunks of
+// consecutive systems.  The iteration reads no right-hand side, so a chunk may span
+// several shifts of a multi-shift refinement (its systems share only the links): with
+// 16 shifts x 2 RHS at 24^3 x 48 the inner iteration takes 8 fields per launch instead
+// of 2 (the links read once per 8 mat-vecs), which with the per-chunk gates and the
+// updates queued behind running systems took the solve from 600 to 369 ms.  A finished system never runs again, so
+// the chunks of a snapshot one poll old never leave out a running one.
+struct Chunk {
+    int j0, nr;
+};
+
+bool system_live(const SysState &q) { return (q.flags & (SYS_RUNNING | SYS_RU_PENDING)) != 0; }
+
+std::vector<Chunk> live_chunks(const CgProblem &P, const std::vector<SysState> &st) {
+    std::vector<Chunk> out;
+    for (int j = 0; j < P.nsys;) {
+        int e = j;
+        while (e < P.nsys && system_live(st[e])) ++e;
+        while (j < e) {
+            const int nr = chunk_of(e - j, P.cap);
+            out.push_back({j, nr});
+            j += nr;
+        }
+        while (j < P.nsys && !system_live(st[j])) ++j;
+    }
+    return out;
+}
+
+// One CG iteration.
 //
 // A solve of one field on a small lattice runs the iteration in four kernels: D_oe,
 // D_eo with the normal-operator epilogue and <p, q> partials, the x / r update that
@@ -368,7 +394,7 @@ constexpr uint32_t kFusedFinishMaxVh = 32768;  // half sites: 16^4 and below
 // the |r|^2 partials of the previous update), and one vector update (p, s = A p, x,
 // r) that leaves the |r|^2 partials for the next iteration; a field on a small lattice
 // finishes both sums in the update's blocks instead, three kernels per iteration.
-int enqueue_cgcg_iteration(const CgProblem &P, CgWork &w, const std::vector<SysState> &st,
+int enqueue_cgcg_iteration(const CgProblem &P, CgWork &w, const std::vector<Chunk> &chunks,
                            hipStream_t s) {
     const bool f64 = P.mode == STG_CG_F64;
     const stg_gauge *gg = f64 ? P.hi : P.lo;
@@ -377,17 +403,11 @@ int enqueue_cgcg_iteration(const CgProblem &P, CgWork &w, const std::vector<SysS
     const bool fused = P.nsys == 1 && P.g.Vh <= kFusedFinishMaxVh;
     const uint32_t nbu = site_blocks(P.g.Vh);                 // blocks of the update kernel
     const size_t rr_buf = (size_t)2 * P.nsys * nbu;           // doubles per rr_partials buffer
-    for (int j0 = 0; j0 < P.nsys;) {
-        const int nr = P.chunk(j0);
-        bool any = false;
-        for (int j = j0; j < j0 + nr; ++j) any = any || (st[j].flags & SYS_RUNNING);
-        if (!any) {
-            j0 += nr;
-            continue;
-        }
+    for (const Chunk &ch : chunks) {
+        const int j0 = ch.j0, nr = ch.nr;
         const size_t o = j0 * fb;
         HopArgs a = base_hop(P.g, gg);
-        a.gate_running = 1;
+        a.gate_mask = SYS_RUNNING;
         a.ctl = w.ctl;
         a.state = w.state + j0;
         a.partials = w.partials;
@@ -419,7 +439,7 @@ int enqueue_cgcg_iteration(const CgProblem &P, CgWork &w, const std::vector<SysS
         v.s = (char *)w.s + o;
         v.state = w.state + j0;
         v.ctl = w.ctl;
-        v.gate_running = 1;
+        v.gate_mask = SYS_RUNNING;
         if (fused) {
             v.fin_partials = w.partials;
             v.fin_blocks = hop_blocks;
@@ -432,37 +452,30 @@ int enqueue_cgcg_iteration(const CgProblem &P, CgWork &w, const std::vector<SysS
             w.rr_cur ^= 1;
         } else {
             double *rrp = w.rr_partials + (size_t)2 * j0 * nbu;
-            FinArgs f{w.partials, hop_blocks, nr, OP_CGCG, 1, w.ctl, w.state + j0, nullptr,
-                      rrp, nbu};
+            FinArgs f{w.partials, hop_blocks, nr, OP_CGCG, SYS_RUNNING, w.ctl, w.state + j0,
+                      nullptr, rrp, nbu};
             VEC_TRY(launch_finalize(f, s));
             v.partials = rrp;
             VEC_TRY(launch_cgcg_update(v, f64, nr, s));
         }
-        j0 += nr;
     }
     HIP_TRY(hipGetLastError());
     return STG_OK;
 }
 
-int enqueue_inner_iteration(const CgProblem &P, CgWork &w, const std::vector<SysState> &st,
+int enqueue_inner_iteration(const CgProblem &P, CgWork &w, const std::vector<Chunk> &chunks,
                             hipStream_t s) {
-    if (P.cgcg) return enqueue_cgcg_iteration(P, w, st, s);
+    if (P.cgcg) return enqueue_cgcg_iteration(P, w, chunks, s);
     const bool f64 = P.mode == STG_CG_F64;
     const stg_gauge *gg = f64 ? P.hi : P.lo;
     const size_t fb = (size_t)3 * P.g.Vh * (f64 ? 16 : 8);
     void *xin = f64 ? P.x : w.x_in;
     const bool fused = P.nsys == 1 && P.g.Vh <= kFusedFinishMaxVh;
-    for (int j0 = 0; j0 < P.nsys;) {
-        const int nr = P.chunk(j0);
-        bool any = false;
-        for (int j = j0; j < j0 + nr; ++j) any = any || (st[j].flags & SYS_RUNNING);
-        if (!any) {
-            j0 += nr;
-            continue;
-        }
+    for (const Chunk &ch : chunks) {
+        const int j0 = ch.j0, nr = ch.nr;
         const size_t o = j0 * fb;
         HopArgs a = base_hop(P.g, gg);
-        a.gate_running = 1;
+        a.gate_mask = SYS_RUNNING;
         a.ctl = w.ctl;
         a.state = w.state + j0;
         a.partials = w.partials;
@@ -495,7 +508,7 @@ int enqueue_inner_iteration(const CgProblem &P, CgWork &w, const std::vector<Sys
         v.state = w.state + j0;
         v.ctl = w.ctl;
         v.partials = w.partials;
-        v.gate_running = 1;
+        v.gate_mask = SYS_RUNNING;
         if (fused) {
             v.fin_partials = w.partials;
             v.fin_blocks = hop_blocks;
@@ -510,20 +523,27 @@ int enqueue_inner_iteration(const CgProblem &P, CgWork &w, const std::vector<Sys
             VEC_TRY(launch_cg_update(v, f64, nr, s));
             VEC_TRY(launch_p_update(v, f64, nr, s));
         }
-        j0 += nr;
     }
     HIP_TRY(hipGetLastError());
     return STG_OK;
 }
 
-// FP64 true-residual update of every parked system: x64 += x_inner (MIXED),
-// r64 = b - A x64, then resume from r64 or finish.
-int enqueue_reliable_update(const CgProblem &P, const CgWork &w, hipStream_t s) {
+// FP64 true-residual update of every parked system of the snapshot st (and of no other:
+// a chunk without one is not launched): x64 += x_inner (MIXED), r64 = b - A x64, then
+// resume from r64 or finish.
+int enqueue_reliable_update(const CgProblem &P, const CgWork &w, const std::vector<SysState> &st,
+                            hipStream_t s) {
     const bool f64 = P.mode == STG_CG_F64;
     const size_t fb64 = (size_t)3 * P.g.Vh * 16;
     const size_t fbin = (size_t)3 * P.g.Vh * (f64 ? 16 : 8);
     for (int j0 = 0; j0 < P.nsys;) {
         const int nr = P.chunk(j0);
+        bool any = false;
+        for (int j = j0; j < j0 + nr; ++j) any = any || (st[j].flags & SYS_RU_PENDING);
+        if (!any) {
+            j0 += nr;
+            continue;
+        }
         VecArgs v;
         std::memset(&v, 0, sizeof(v));
         v.Vh = P.g.Vh;
@@ -537,6 +557,7 @@ int enqueue_reliable_update(const CgProblem &P, const CgWork &w, hipStream_t s) 
             VEC_TRY(launch_ru_accumulate(v, nr, s));
         }
         HopArgs a = base_hop(P.g, P.hi);
+        a.gate_mask = SYS_RU_PENDING;
         a.ctl = w.ctl;
         a.state = w.state + j0;
         a.partials = w.partials;
@@ -638,6 +659,16 @@ int read_states(const CgWork &w, int nsys, std::vector<SysState> &st, hipStream_
     return read_states_n(w.state, nsys, st, s);
 }
 
+// Iterations queued between two looks at the flags.  One field: about 4 million site
+// updates (8 to 64 iterations).  Several: the same work shared by the live systems, at
+// least 4 iterations, since a system parked for its true-residual update waits, in every
+// launch of its chunk, until the host has seen it.
+int poll_iterations(const CgProblem &P, int live) {
+    if (P.prm.poll_every > 0) return P.prm.poll_every;
+    const uint32_t work = (1u << 22) / P.g.Vh / (uint32_t)std::max(live, 1);
+    return (int)std::min<uint32_t>(64, std::max<uint32_t>(live > 1 ? 4 : 8, work));
+}
+
 int run_cg(const CgProblem &P, CgWork w, stg_cg_stats *stats, hipStream_t s) {
     const auto t0 = std::chrono::steady_clock::now();
     const int n = P.nsys;
@@ -690,54 +721,80 @@ int run_cg(const CgProblem &P, CgWork w, stg_cg_stats *stats, hipStream_t s) {
     }
     if (any_zero)
         HIP_TRY(hipMemcpyAsync(w.state, st.data(), sizeof(SysState) * n, hipMemcpyHostToDevice, s));
-    rc = enqueue_reliable_update(P, w, s);
+    rc = enqueue_reliable_update(P, w, st, s);
     if (rc) return rc;
 
-    int poll = P.prm.poll_every;
-    if (poll <= 0) poll = (int)std::min<uint32_t>(64, std::max<uint32_t>(8, (1u << 22) / P.g.Vh));
     int status_all = STG_OK;
     rc = snapshots_ready(n);
     if (rc) return rc;
-    // Pipelined polling: chunk c+1 is queued before the flags copied after chunk c
-    // are read, so the GPU never waits for the host.  A parked system (reliable
-    // update due) sees its update after at most one more chunk, in which it does
-    // not iterate; the update itself drains the stream and restarts the pipeline.
+    // Pipelined polling: the next run of iterations is queued before the flags copied
+    // after the last one are read, so the GPU never waits for the host.  A parked system
+    // (reliable update due) gets its update as soon as the host has seen it parked; while
+    // other systems run, the update is queued behind the iterations in flight and they
+    // go on.  Only when every system left is parked does the update drain the stream, so
+    // that the solve ends on fresh flags.  sent[j]: the last snapshot that can still show
+    // system j parked although its update has been queued.
     rc = read_states(w, n, st, s);
     if (rc) return rc;
     int slot = 0, pend = -1;  // pend: slot of a queued snapshot not read yet
+    int queued = 0, seen = 0; // snapshots queued; the one st holds
+    std::vector<int> sent(n, -1);
     StallGuard guard;
     for (;;) {
-        int running = 0, pending = 0;
+        int running = 0, pending = 0, live = 0;
         for (int j = 0; j < n; ++j) {
+            if ((st[j].flags & SYS_RU_PENDING) && seen <= sent[j]) {
+                ++running;  // its update is on the way
+                ++live;
+                continue;
+            }
             if (st[j].flags & SYS_RUNNING) ++running;
             if (st[j].flags & SYS_RU_PENDING) ++pending;
+            live += system_live(st[j]) ? 1 : 0;
         }
-        if (pending) {
+        if (pending && !running) {
             if (pend >= 0) {
-                rc = snapshot_wait(n, pend, st);  // the chunk queued after it: done, unused
+                rc = snapshot_wait(n, pend, st);  // the run queued after it: done, unused
                 if (rc) return rc;
                 pend = -1;
             }
-            rc = enqueue_reliable_update(P, w, s);
+            rc = enqueue_reliable_update(P, w, st, s);
             if (rc) return rc;
             rc = read_states(w, n, st, s);
             if (rc) return rc;
+            seen = queued + 1;  // newer than every update so far
             continue;
         }
-        if (running == 0) break;
+        if (!running) break;
         if (guard.stalled(st)) {
             (void)hipStreamSynchronize(s);
             return stall_error();
         }
+        if (pending) {
+            std::vector<SysState> due = st;
+            for (int j = 0; j < n; ++j) {
+                if (!(st[j].flags & SYS_RU_PENDING)) continue;
+                if (seen <= sent[j])
+                    due[j].flags = 0;
+                else
+                    sent[j] = queued;
+            }
+            rc = enqueue_reliable_update(P, w, due, s);
+            if (rc) return rc;
+        }
+        const std::vector<Chunk> chunks = live_chunks(P, st);
+        const int poll = poll_iterations(P, live);
         for (int i = 0; i < poll; ++i) {
-            rc = enqueue_inner_iteration(P, w, st, s);
+            rc = enqueue_inner_iteration(P, w, chunks, s);
             if (rc) return rc;
         }
         rc = snapshot_enqueue(w.state, n, slot, s);
         if (rc) return rc;
+        ++queued;
         if (pend >= 0) {
-            rc = snapshot_wait(n, pend, st);  // flags one chunk behind the queue
+            rc = snapshot_wait(n, pend, st);  // flags one run behind the queue
             if (rc) return rc;
+            seen = queued - 1;
         }
         pend = slot;
         slot ^= 1;
@@ -756,7 +813,7 @@ int run_cg(const CgProblem &P, CgWork w, stg_cg_stats *stats, hipStream_t s) {
         }
     if (any_open) {
         HIP_TRY(hipMemcpyAsync(w.state, st.data(), sizeof(SysState) * n, hipMemcpyHostToDevice, s));
-        rc = enqueue_reliable_update(P, w, s);
+        rc = enqueue_reliable_update(P, w, st, s);
         if (rc) return rc;
         rc = read_states(w, n, st, s);
         if (rc) return rc;
@@ -859,7 +916,7 @@ int enqueue_ms_iteration(const Geom &g, const stg_gauge *gg, int f64, int nrhs, 
         const int nr = chunk_of(nrhs - j0, cap);
         const size_t o = j0 * fb;
         HopArgs a = base_hop(g, gg);
-        a.gate_running = 1;
+        a.gate_mask = SYS_RUNNING | SYS_FINISHING;
         a.ctl = w.ctl;
         a.state = w.state + j0;
         a.partials = w.partials;
@@ -889,7 +946,7 @@ int enqueue_ms_iteration(const Geom &g, const stg_gauge *gg, int f64, int nrhs, 
         v.state = w.state + j0;
         v.ctl = w.ctl;
         v.partials = w.partials;
-        v.gate_running = 1;
+        v.gate_mask = SYS_RUNNING | SYS_FINISHING;
         VEC_TRY(launch_ms_r_update(v, f64, nr, s));
         VEC_TRY(launch_ms_p_update(v, f64, nr, s));
         j0 += nr;

@@ -33,7 +33,7 @@ namespace stg {
 
 template <typename T, int FMT, bool STDPH, int NR, int EPI, bool STAGE, bool MULTI>
 __global__ __launch_bounds__(kBlock) void hop_kernel(HopArgs a) {
-    if (a.gate_running && a.ctl->n_running == 0) return;
+    if (gate_closed<NR>(a.state, a.gate_mask)) return;
 
     const Geom &g = a.geom;
     const uint32_t blk = a.xcd_remap ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
@@ -121,7 +121,7 @@ static int launch_nr(const HopArgs &a, int epi, hipStream_t stream) {
         launch_multi<T, FMT, STDPH, NR, false>(a, epi, grid, stream);
     if (a.grid_out) *a.grid_out = grid.x;
     if (reduce && !a.defer_finish) {
-        FinArgs f{a.partials, grid.x, NR, a.op, a.gate_running, a.ctl, a.state, a.out_sums};
+        FinArgs f{a.partials, grid.x, NR, a.op, a.gate_mask, a.ctl, a.state, a.out_sums};
         launch_finalize(f, stream);
     }
     return 0;

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * (NR / FPG)) void hop_fsplit_kernel(HopArgs a) 
     constexpr int W = LinkWords<T, FMT>::W;
     static_assert(NR % FPG == 0, "fields per wave must divide the fields of the launch");
     static_assert(fsplit_lds_bytes<T, FMT>() <= kSplitLdsMax, "link tile exceeds the LDS budget");
-    if (a.gate_running && a.ctl->n_running == 0) return;
+    if (gate_closed<NR>(a.state, a.gate_mask)) return;
     // [slot 2 d + (0 forward, 1 backward)][word][site]: lanes read consecutive words
     __shared__ nu4 tile[8][W][kFsSites];
 
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(64 * (NR / FPG)) void hop_fsplit_dec_kernel(HopArgs
     constexpr int G = NR / FPG;
     static_assert(NR % FPG == 0, "fields per wave must divide the fields of the launch");
     static_assert(kFsDecLdsBytes <= kSplitLdsMax, "link tile exceeds the LDS budget");
-    if (a.gate_running && a.ctl->n_running == 0) return;
+    if (gate_closed<NR>(a.state, a.gate_mask)) return;
     // [slot 2 d + (0 forward, 1 backward)][entry 3 row + column][site]
     __shared__ cpx<float> ltile[8][9][kFsSites];
     __shared__ uint32_t ntile[8][kFsSites];
@@ -403,7 +403,7 @@ static int launch_fpg(const HopArgs &a, int epi, hipStream_t stream) {
         }
         if (a.grid_out) *a.grid_out = grid.x;
         if (reduce && !a.defer_finish) {
-            FinArgs f{a.partials, grid.x, NR, a.op, a.gate_running, a.ctl, a.state, a.out_sums};
+            FinArgs f{a.partials, grid.x, NR, a.op, a.gate_mask, a.ctl, a.state, a.out_sums};
             launch_finalize(f, stream);
         }
         return 0;

@@ -40,7 +40,7 @@ __host__ __device__ constexpr int spread_owner(int j) { return j / (NR / TPS); }
 
 template <typename T, int FMT, bool STDPH, int NR, int EPI, int TPS, bool SPREAD>
 __global__ __launch_bounds__(kBlock) void hop_split_kernel(HopArgs a) {
-    if (a.gate_running && a.ctl->n_running == 0) return;
+    if (gate_closed<NR>(a.state, a.gate_mask)) return;
     constexpr int SPB = kBlock / TPS;  // sites per block, a multiple of the wave size
     constexpr int DPT = 4 / TPS;       // directions per thread
     static_assert(split_lds_bytes(sizeof(cpx<T>), NR, TPS) <= kSplitLdsMax,
@@ -176,7 +176,7 @@ static int launch_tps(const HopArgs &a, int epi, hipStream_t stream) {
     }
     if (a.grid_out) *a.grid_out = grid.x;
     if (reduce && !a.defer_finish) {
-        FinArgs f{a.partials, grid.x, NR, a.op, a.gate_running, a.ctl, a.state, a.out_sums};
+        FinArgs f{a.partials, grid.x, NR, a.op, a.gate_mask, a.ctl, a.state, a.out_sums};
         launch_finalize(f, stream);
     }
     return 0;

@@ -23,7 +23,8 @@ struct HopArgs {
     size_t fstride;       // complex elements between consecutive fields
     int out_parity;       // 0: D_eo (even outputs), 1: D_oe (odd outputs)
     int op;               // FinOp of the reduction (OP_NONE: no reduction)
-    int gate_running;     // exit at once when ctl->n_running == 0
+    int gate_mask;        // exit at once when no system of the launch has one of these
+                          // flags (0: no gate)
     int xcd_remap;        // 1: blocks of one XCD take one contiguous range of sites
     uint32_t sites_per_thread;  // each block covers this many consecutive kBlock-site chunks
     uint32_t stage_neighbours;  // 1: x0/x1 neighbour fields read from an LDS copy
@@ -84,7 +85,7 @@ struct FinArgs {
     uint32_t nblocks;
     int nr;
     int op;
-    int gate_running;
+    int gate_mask;        // a block leaves when its system has none of these flags (0: no gate)
     Ctl *ctl;
     SysState *state;
     double *out;
@@ -206,7 +207,7 @@ struct VecArgs {
     SysState *state;
     Ctl *ctl;
     double *partials;
-    int gate_running;
+    int gate_mask;        // as in HopArgs; the fused single-field kernels gate on ctl->n_running
     int op;
     // multi-shift: shifted solutions and directions, [nshift][nrhs][3][Vh]
     void *xs;

@@ -86,6 +86,22 @@ enum FinOp {
     OP_CGCG = 8      // single-reduction CG: sums = <r, A r>, sums2 = |r|^2 -> alpha, beta
 };
 
+// Gate of a launch over NR systems: closed when none of them has a flag of mask, so
+// that a chunk of fields whose systems are all parked or finished costs a launch and
+// not its memory traffic while other chunks of the solve still run.  The flags are
+// uniform loads issued together; no block of the launch changes them.  (Gating on the
+// solve's running count instead kept every chunk working until the last system of the
+// solve had stopped: with 16 shifts x 2 RHS at 24^3 x 48, 4128 launches of 2 fields per
+// kernel in the refinement where about 2600 had a running system.)
+template <int NR>
+__device__ __forceinline__ bool gate_closed(const SysState *state, int mask) {
+    if (!mask) return false;
+    int any = 0;
+#pragma unroll
+    for (int j = 0; j < NR; ++j) any |= state[j].flags;
+    return (any & mask) == 0;
+}
+
 // Gate of the kernels that finish reductions: other blocks of the same launch may
 // change the running count meanwhile, so one thread reads it and the whole block
 // takes the same branch (every wave then reaches the same barriers).  A block whose
