@@ -306,7 +306,8 @@ __global__ __launch_bounds__(kBlock) void ru_resume_kernel(VecArgs a) {
     }
 }
 
-// multi-shift (Sec. 2.2, Eq. shlineq): base residual r -= alpha q; |r|^2 -> OP_MS_BETA
+// multi-shift (Sec. 2.2, Eq. shlineq): base residual r = r_in - alpha q (the next slot of
+// the ring of residuals); |r|^2 -> OP_MS_BETA
 template <typename T, int NR>
 __global__ __launch_bounds__(kBlock) void ms_r_update_kernel(VecArgs a) {
     if (gate_closed<NR>(a.state, a.gate_mask)) return;
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(kBlock) void ms_r_update_kernel(VecArgs a) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const size_t i = (size_t)j * a.fstride + (size_t)c * a.Vh + h;
-            cpx<T> r = ld_c<T>(a.r, i), q = ld_c<T>(a.q, i);
+            cpx<T> r = ld_c<T>(a.r_in, i), q = ld_c<T>(a.q, i);
             r.re -= al * q.re;
             r.im -= al * q.im;
             st_c<T>(a.r, i, r);
@@ -332,77 +333,73 @@ __global__ __launch_bounds__(kBlock) void ms_r_update_kernel(VecArgs a) {
     }
     block_partials<NR>(ps, pc, a.partials);
 }
-
-// multi-shift, after beta: every shift that took part in this iteration steps
-// x_k += alpha_k p_k with its old p_k, then the still active ones p_k = zeta_k r +
-// beta_k p_k (one read of p_k for both); the base p = r + beta p.
+// multi-shift, every M iterations: the steps of the shifted systems that the iterations
+// left in a.steps (solver_state.hpp ShiftStep), x_k += alpha_k p_k with the old p_k, then
+// p_k = zeta_k r + beta_k p_k with that iteration's base residual r, one slot of the ring
+// a.r after the other.  The same operations in the same order as when every iteration
+// updates the shifted vectors, but x_k and p_k are read and written once for M
+// iterations: the update was bound by that traffic (4 vectors per active shift and
+// iteration, 68 % of the stage's bytes with 16 shifts), which M = 8 divides by eight.
+// 16^3 x 32, 10 poles x 4 RHS in FP64: 37.1 us per iteration with the base directions ->
+// 48.8 / 8 + 7.2 (the whole solve 68.9 -> 52.2 ms); 24^3 x 48, 16 shifts x 2 RHS in FP32:
+// 58.4 -> 106 / 8 + 8.5 us.
 //
-// One block works on one chunk of kBlock sites for one shift (or, for the last
-// index, the base directions), so every (shift, RHS) pair is its own streamed pass
-// over its two fields and a retired shift costs one scalar test per block.  The
-// shift blocks of a site chunk sit next to each other in the XCD-ordered block
-// sequence: they run on the same XCD, where the base residual r they all read
-// stays in L2.
-template <typename T, int NR>
-__global__ __launch_bounds__(kBlock) void ms_p_update_kernel(VecArgs a) {
-    if (gate_closed<NR>(a.state, a.gate_mask)) return;
-    const uint32_t nk = (uint32_t)a.nshift + 1;
-    const uint32_t lb = xcd_block(blockIdx.x, gridDim.x);
-    const uint32_t k = lb % nk;
-    const uint32_t h = (lb / nk) * kBlock + threadIdx.x;
+// One block works on one chunk of kBlock sites of one (shift, RHS) pair; a retired pair
+// costs one scalar test per block.  The shift blocks of a chunk sit next to each other in
+// the XCD-ordered block sequence: they run on the same XCD, where the residuals they all
+// read stay in L2.
+template <typename T, int M>
+__global__ __launch_bounds__(kBlock) void ms_shift_update_kernel(VecArgs a) {
+    const uint32_t nk = (uint32_t)a.nshift;
+    uint32_t b = xcd_block(blockIdx.x, gridDim.x);
+    const uint32_t k = b % nk;
+    b /= nk;
+    const uint32_t nr = (uint32_t)a.nfields;
+    const uint32_t j = b % nr;
+    const uint32_t h = (b / nr) * kBlock + threadIdx.x;
     const Ctl &ctl = *a.ctl;
-    if (k == (uint32_t)a.nshift) {  // base directions of the running systems
-        if (h >= a.Vh) return;
+    const size_t slot = (size_t)ctl.nshift * ctl.nrhs;  // entries per slot of steps
+    const ShiftStep *st = ctl.steps + k * ctl.nrhs + a.state[j].gid;
+    if (st[0].mode == 0 || h >= a.Vh) return;  // the modes of a pair never rise again
+    const bool both = st[0].mode == 2;
+    const size_t ir = (size_t)j * a.fstride + h, i = (size_t)k * a.kstride + ir;
+    vec3<T> x, p, r[M];
 #pragma unroll
-        for (int j = 0; j < NR; ++j) {
-            const SysState &s = a.state[j];
-            if (!(s.flags & SYS_RUNNING)) continue;
-            const T be = (T)s.beta;
+    for (int c = 0; c < 3; ++c) x.c[c] = ld_c<T>(a.xs, i + (size_t)c * a.Vh);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const size_t i = (size_t)j * a.fstride + (size_t)c * a.Vh + h;
-                cpx<T> p = ld_c<T>(a.p, i), r = ld_c<T>(a.r, i);
-                p.re = r.re + be * p.re;
-                p.im = r.im + be * p.im;
-                st_c<T>(a.p, i, p);
-            }
+    for (int c = 0; c < 3; ++c) p.c[c] = ld_c<T>(a.ps, i + (size_t)c * a.Vh);
+    // the residuals of all the steps that need one are loaded before the first step
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+        if (m < a.nsteps && st[m * slot].mode == 2) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                r[m].c[c] = ld_c<T>(a.r, (size_t)m * a.rstride + ir + (size_t)c * a.Vh);
         }
-        return;
-    }
-    // this shift for every RHS: wave-uniform tests, the loads of all its active
-    // systems issued together
-    bool any = false;
 #pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        const SysState &s = a.state[j];
-        const bool part = (s.flags & (SYS_RUNNING | SYS_FINISHING)) != 0;
-        any = any || (part && ctl.ms[k * ctl.nrhs + s.gid].active != 0);
-    }
-    if (!any || h >= a.Vh) return;
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        const SysState &s = a.state[j];
-        const bool running = (s.flags & SYS_RUNNING) != 0;
-        if (!running && !(s.flags & SYS_FINISHING)) continue;
-        const ShiftState &z = ctl.ms[k * ctl.nrhs + s.gid];
-        if (!z.active) continue;
-        const bool more = running && z.active == 1;
+    for (int m = 0; m < M; ++m) {
+        if (m >= a.nsteps) break;
+        const ShiftStep &z = st[m * slot];
+        if (z.mode == 0) break;
         const T ak = (T)z.alpha, zk = (T)z.zeta, bk = (T)z.beta;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const size_t ir = (size_t)j * a.fstride + (size_t)c * a.Vh + h;
-            const size_t i = (size_t)k * a.kstride + ir;
-            cpx<T> p = ld_c<T>(a.ps, i), x = ld_c<T>(a.xs, i);
-            x.re += ak * p.re;
-            x.im += ak * p.im;
-            st_c<T>(a.xs, i, x);
-            if (more) {
-                const cpx<T> r = ld_c<T>(a.r, ir);
-                p.re = zk * r.re + bk * p.re;
-                p.im = zk * r.im + bk * p.im;
-                st_c<T>(a.ps, i, p);
+            x.c[c].re += ak * p.c[c].re;
+            x.c[c].im += ak * p.c[c].im;
+        }
+        if (z.mode == 2) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                p.c[c].re = zk * r[m].c[c].re + bk * p.c[c].re;
+                p.c[c].im = zk * r[m].c[c].im + bk * p.c[c].im;
             }
         }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) st_c<T>(a.xs, i + (size_t)c * a.Vh, x.c[c]);
+    if (both) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) st_c<T>(a.ps, i + (size_t)c * a.Vh, p.c[c]);
     }
 }
 
@@ -437,28 +434,27 @@ int launch_cg_update(const VecArgs &a, int fp64, int nr, hipStream_t stream) {
     return launch_finalize(f, stream);
 }
 
-// grid: (nshift + 1) blocks per chunk of kBlock sites
-int launch_ms_p_update(const VecArgs &a, int fp64, int nr, hipStream_t stream) {
-    dim3 grid(site_blocks(a.Vh) * (uint32_t)(a.nshift + 1));
-    switch (nr * 2 + (fp64 ? 1 : 0)) {
-        case 3: ms_p_update_kernel<double, 1><<<grid, kBlock, 0, stream>>>(a); return 0;
-        case 2: ms_p_update_kernel<float, 1><<<grid, kBlock, 0, stream>>>(a); return 0;
-        case 5: ms_p_update_kernel<double, 2><<<grid, kBlock, 0, stream>>>(a); return 0;
-        case 4: ms_p_update_kernel<float, 2><<<grid, kBlock, 0, stream>>>(a); return 0;
-        case 7: ms_p_update_kernel<double, 3><<<grid, kBlock, 0, stream>>>(a); return 0;
-        case 6: ms_p_update_kernel<float, 3><<<grid, kBlock, 0, stream>>>(a); return 0;
-        case 9: ms_p_update_kernel<double, 4><<<grid, kBlock, 0, stream>>>(a); return 0;
-        case 8: ms_p_update_kernel<float, 4><<<grid, kBlock, 0, stream>>>(a); return 0;
-        case 17: ms_p_update_kernel<double, 8><<<grid, kBlock, 0, stream>>>(a); return 0;
-        case 16: ms_p_update_kernel<float, 8><<<grid, kBlock, 0, stream>>>(a); return 0;
+// grid: one block per (chunk of kBlock sites, field, shift)
+int launch_ms_shift_update(const VecArgs &a, int fp64, int slots, hipStream_t stream) {
+    dim3 grid(site_blocks(a.Vh) * (uint32_t)(a.nshift * a.nfields));
+    switch (slots * 2 + (fp64 ? 1 : 0)) {
+        case 3: ms_shift_update_kernel<double, 1><<<grid, kBlock, 0, stream>>>(a); return 0;
+        case 2: ms_shift_update_kernel<float, 1><<<grid, kBlock, 0, stream>>>(a); return 0;
+        case 5: ms_shift_update_kernel<double, 2><<<grid, kBlock, 0, stream>>>(a); return 0;
+        case 4: ms_shift_update_kernel<float, 2><<<grid, kBlock, 0, stream>>>(a); return 0;
+        case 9: ms_shift_update_kernel<double, 4><<<grid, kBlock, 0, stream>>>(a); return 0;
+        case 8: ms_shift_update_kernel<float, 4><<<grid, kBlock, 0, stream>>>(a); return 0;
+        case 17: ms_shift_update_kernel<double, 8><<<grid, kBlock, 0, stream>>>(a); return 0;
+        case 16: ms_shift_update_kernel<float, 8><<<grid, kBlock, 0, stream>>>(a); return 0;
         default: return -1;
     }
 }
 
 int launch_ms_r_update(const VecArgs &a, int fp64, int nr, hipStream_t stream) {
     if (launch_ms_r_update_only(a, fp64, nr, stream)) return -1;
-    FinArgs f{a.partials, site_blocks(a.Vh), nr, OP_MS_BETA, a.gate_mask, a.ctl, a.state,
-              nullptr};
+    // no gate: the iteration's slot of the deferred shift steps is written in any case
+    FinArgs f{a.partials, site_blocks(a.Vh), nr, OP_MS_BETA, 0, a.ctl, a.state, nullptr};
+    f.slot = a.slot;
     return launch_finalize(f, stream);
 }
 
@@ -476,7 +472,7 @@ __global__ __launch_bounds__(kBlock) void finalize_kernel(FinArgs f) {
     if (f.op == OP_CGCG)
         tot2 = block_sum2_pairs(f.partials2 + 2 * (size_t)j * f.nblocks2, (int)f.nblocks2, sh_red);
     if (f.op == OP_MS_ALPHA || f.op == OP_MS_BETA)
-        finalize_ms_block(f.op, f.ctl, f.state, j, tot);
+        finalize_ms_block(f.op, f.ctl, f.state, j, tot, f.slot);
     else if (threadIdx.x == 0)
         finalize_one(f.op, f.ctl, f.state, f.out, j, tot, tot2);
 }

@@ -878,23 +878,28 @@ struct MsWork {
     Ctl *ctl;
     SysState *state;      // one per RHS: the base system
     ShiftState *shift;    // [nshift][nrhs]
+    ShiftStep *steps;     // the iterations' steps of the shifts, [slots][nshift][nrhs]
     double *partials;
-    void *p, *r, *q, *t;  // base vectors, inner precision, [nrhs]
+    void *p, *q, *t;      // base vectors, inner precision, [nrhs]
+    void *r;              // ring of base residuals, [slots][nrhs]
+    int slots;            // iterations between two updates of the shifted vectors
     void *xs, *ps;        // shifted solutions and directions, inner precision, [nshift][nrhs]
     size_t bytes;
 };
 
-MsWork carve_ms(const Geom &g, int nrhs, int nshift, int mode, void *ws) {
+MsWork carve_ms_slots(const Geom &g, int nrhs, int nshift, int mode, int slots, void *ws) {
     Carver c{reinterpret_cast<char *>(ws)};
     MsWork w;
+    w.slots = slots;
     const size_t e = mode == STG_CG_F64 ? 16 : 8;
     const size_t f1 = (size_t)nrhs * 3 * g.Vh * e;
     w.ctl = (Ctl *)c.take(sizeof(Ctl));
     w.state = (SysState *)c.take(sizeof(SysState) * (size_t)nrhs);
     w.shift = (ShiftState *)c.take(sizeof(ShiftState) * (size_t)nrhs * nshift);
+    w.steps = (ShiftStep *)c.take(sizeof(ShiftStep) * (size_t)slots * nrhs * nshift);
     w.partials = (double *)c.take(sizeof(double) * partial_count(g));
     w.p = c.take(f1);
-    w.r = c.take(f1);
+    w.r = c.take(f1 * slots);
     w.q = c.take(f1);
     w.t = c.take(f1);
     w.xs = c.take(f1 * nshift);
@@ -903,13 +908,49 @@ MsWork carve_ms(const Geom &g, int nrhs, int nshift, int mode, void *ws) {
     return w;
 }
 
+// The shifted vectors are updated once for as many iterations (8, 4, 2 or 1) as there is
+// room for residuals in the workspace that the refinement needs anyway: 8 from four
+// shifts on (mixed: from two), so the solve asks for no more memory than with 1.
+MsWork carve_ms(const Geom &g, int nrhs, int nshift, int mode, void *ws) {
+    const size_t room = std::max(carve_ms_slots(g, nrhs, nshift, mode, 1, nullptr).bytes,
+                                 carve_cg(g, nrhs * nshift, mode, nullptr).bytes);
+    int slots = 8;
+    while (slots > 1 && carve_ms_slots(g, nrhs, nshift, mode, slots, nullptr).bytes > room)
+        slots /= 2;
+    return carve_ms_slots(g, nrhs, nshift, mode, slots, ws);
+}
+
 size_t ms_workspace(const Geom &g, int nrhs, int nshift, int mode) {
     return std::max(carve_ms(g, nrhs, nshift, mode, nullptr).bytes,
                     carve_cg(g, nrhs * nshift, mode, nullptr).bytes);
 }
 
+// The deferred steps of the first `steps` slots on every shifted system.
+int enqueue_ms_shift_update(const Geom &g, int f64, int nrhs, int nshift, const MsWork &w,
+                            int steps, hipStream_t s) {
+    VecArgs v;
+    std::memset(&v, 0, sizeof(v));
+    v.Vh = g.Vh;
+    v.fstride = (size_t)3 * g.Vh;
+    v.r = w.r;
+    v.rstride = (size_t)nrhs * 3 * g.Vh;
+    v.xs = w.xs;
+    v.ps = w.ps;
+    v.kstride = (size_t)nrhs * 3 * g.Vh;
+    v.nshift = nshift;
+    v.nfields = nrhs;
+    v.nsteps = steps;
+    v.state = w.state;
+    v.ctl = w.ctl;
+    VEC_TRY(launch_ms_shift_update(v, f64, w.slots, s));
+    HIP_TRY(hipGetLastError());
+    return STG_OK;
+}
+
+// One base iteration into slot `slot` of the ring of residuals, then the shifted
+// systems' steps of the whole ring when it is the last slot.
 int enqueue_ms_iteration(const Geom &g, const stg_gauge *gg, int f64, int nrhs, int nshift,
-                         const MsWork &w, hipStream_t s) {
+                         const MsWork &w, int slot, hipStream_t s) {
     const size_t fb = (size_t)3 * g.Vh * (f64 ? 16 : 8);
     const int cap = field_cap(g, gg->fmt);
     for (int j0 = 0; j0 < nrhs;) {
@@ -937,22 +978,21 @@ int enqueue_ms_iteration(const Geom &g, const stg_gauge *gg, int f64, int nrhs, 
         v.Vh = g.Vh;
         v.fstride = (size_t)3 * g.Vh;
         v.p = (char *)w.p + o;
-        v.r = (char *)w.r + o;
+        v.r_in = (char *)w.r + (size_t)(slot ? slot - 1 : w.slots - 1) * nrhs * fb + o;
+        v.r = (char *)w.r + (size_t)slot * nrhs * fb + o;
         v.q = (const char *)w.q + o;
-        v.xs = (char *)w.xs + o;
-        v.ps = (char *)w.ps + o;
-        v.kstride = (size_t)nrhs * 3 * g.Vh;
-        v.nshift = nshift;
+        v.slot = slot;
         v.state = w.state + j0;
         v.ctl = w.ctl;
         v.partials = w.partials;
-        v.gate_mask = SYS_RUNNING | SYS_FINISHING;
+        v.gate_mask = SYS_RUNNING;
         VEC_TRY(launch_ms_r_update(v, f64, nr, s));
-        VEC_TRY(launch_ms_p_update(v, f64, nr, s));
+        VEC_TRY(launch_p_update(v, f64, nr, s));
         j0 += nr;
     }
     HIP_TRY(hipGetLastError());
-    return STG_OK;
+    if (slot + 1 < w.slots) return STG_OK;
+    return enqueue_ms_shift_update(g, f64, nrhs, nshift, w, w.slots, s);
 }
 
 int run_mscg(const Geom &g, const stg_gauge *hi, const stg_gauge *lo, double mass, int nshift,
@@ -979,6 +1019,7 @@ int run_mscg(const Geom &g, const stg_gauge *hi, const stg_gauge *lo, double mas
     ctl0.nshift = nshift;
     ctl0.nrhs = nrhs;
     ctl0.ms = w.shift;
+    ctl0.steps = w.steps;
     std::vector<SysState> st(nrhs);
     for (int j = 0; j < nrhs; ++j) {
         SysState &q = st[j];
@@ -1004,15 +1045,17 @@ int run_mscg(const Geom &g, const stg_gauge *hi, const stg_gauge *lo, double mas
     HIP_TRY(hipMemcpyAsync(w.state, st.data(), sizeof(SysState) * nrhs, hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(w.shift, zs.data(), sizeof(ShiftState) * zs.size(),
                            hipMemcpyHostToDevice, s));
-    // r = p = b, p_k = b, x_k = 0  (in the inner precision)
+    // r = p = b, p_k = b, x_k = 0  (in the inner precision); the first iteration reads r
+    // from the last slot of the ring
+    char *r0 = (char *)w.r + (size_t)(w.slots - 1) * nrhs * fbin;
     if (f64) {
-        HIP_TRY(hipMemcpyAsync(w.r, b, nrhs * fb64, hipMemcpyDeviceToDevice, s));
+        HIP_TRY(hipMemcpyAsync(r0, b, nrhs * fb64, hipMemcpyDeviceToDevice, s));
     } else {
-        launch_c128_to_c64((size_t)nrhs * n1, b, w.r, s);
+        launch_c128_to_c64((size_t)nrhs * n1, b, r0, s);
     }
-    HIP_TRY(hipMemcpyAsync(w.p, w.r, nrhs * fbin, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(hipMemcpyAsync(w.p, r0, nrhs * fbin, hipMemcpyDeviceToDevice, s));
     for (int k = 0; k < nshift; ++k)
-        HIP_TRY(hipMemcpyAsync((char *)w.ps + (size_t)k * nrhs * fbin, w.r, nrhs * fbin,
+        HIP_TRY(hipMemcpyAsync((char *)w.ps + (size_t)k * nrhs * fbin, r0, nrhs * fbin,
                                hipMemcpyDeviceToDevice, s));
     launch_zero(w.xs, (size_t)nshift * nrhs * fbin, s);
     for (int j = 0; j < nrhs; ++j) {
@@ -1051,6 +1094,7 @@ int run_mscg(const Geom &g, const stg_gauge *hi, const stg_gauge *lo, double mas
     // pipelined polling as in the CG loop (no reliable updates in this stage; the
     // iteration cap is enforced on the device)
     int slot = 0, pend = -1;
+    int ring = 0;  // slot of the next iteration
     StallGuard guard;
     for (;;) {
         int running = 0;
@@ -1062,8 +1106,9 @@ int run_mscg(const Geom &g, const stg_gauge *hi, const stg_gauge *lo, double mas
             return stall_error();
         }
         for (int i = 0; i < poll; ++i) {
-            rc = enqueue_ms_iteration(g, gg, f64, nrhs, nshift, w, s);
+            rc = enqueue_ms_iteration(g, gg, f64, nrhs, nshift, w, ring, s);
             if (rc) return rc;
+            ring = (ring + 1) % w.slots;
         }
         rc = snapshot_enqueue(w.state, nrhs, slot, s);
         if (rc) return rc;
@@ -1073,6 +1118,10 @@ int run_mscg(const Geom &g, const stg_gauge *hi, const stg_gauge *lo, double mas
         }
         pend = slot;
         slot ^= 1;
+    }
+    if (ring > 0) {  // the steps of the iterations since the last full ring
+        rc = enqueue_ms_shift_update(g, f64, nrhs, nshift, w, ring, s);
+        if (rc) return rc;
     }
     HIP_TRY(hipStreamSynchronize(s));
     rc = read_states_n(w.state, nrhs, st, s);

@@ -91,6 +91,7 @@ struct FinArgs {
     double *out;
     const double *partials2;  // OP_CGCG: the |r|^2 partials, [nr][nblocks2][2]
     uint32_t nblocks2;
+    int slot;                 // OP_MS_BETA: slot of the deferred shift steps
 };
 int launch_finalize(const FinArgs &f, hipStream_t stream);
 
@@ -214,7 +215,13 @@ struct VecArgs {
     void *ps;
     size_t kstride;       // complex elements between shifts (nrhs * 3 * Vh)
     int nshift;
-    int pad2_;
+    int nfields;          // shift update: fields (RHS) of the launch
+    // multi-shift: the ring of base residuals that the deferred steps read (r: slot 0 in
+    // the shift update, the written slot in the r update)
+    const void *r_in;     // r update: the previous iteration's slot
+    size_t rstride;       // shift update: complex elements between slots
+    int slot;             // r update: the slot it writes
+    int nsteps;           // shift update: slots to apply
     // single-field CG with the reductions finished in the consumers: the block
     // partials of the previous kernel, and the state buffer the next iteration reads
     const double *fin_partials;
@@ -255,10 +262,11 @@ int launch_ru_accumulate(const VecArgs &a, int nr, hipStream_t stream);
 // r_inner = r64 (rounded); p = r_inner + beta p  (systems just resumed)
 int launch_ru_resume(const VecArgs &a, int fp64, int nr, hipStream_t stream);
 
-// multi-shift: r -= alpha q; |r|^2 -> OP_MS_BETA
+// multi-shift: r = r_in - alpha q; |r|^2 -> OP_MS_BETA
 int launch_ms_r_update(const VecArgs &a, int fp64, int nr, hipStream_t stream);
-// multi-shift: x_k += alpha_k p_k; p = r + beta p; p_k = zeta_k r + beta_k p_k
-int launch_ms_p_update(const VecArgs &a, int fp64, int nr, hipStream_t stream);
+// multi-shift: the last a.nsteps iterations' x_k += alpha_k p_k and p_k = zeta_k r +
+// beta_k p_k, from a ring of `slots` (1, 2, 4 or 8) residuals
+int launch_ms_shift_update(const VecArgs &a, int fp64, int slots, hipStream_t stream);
 // dst (complex128) = src (complex64), n complex entries
 int launch_c64_to_c128(size_t n, const void *src, void *dst, hipStream_t stream);
 

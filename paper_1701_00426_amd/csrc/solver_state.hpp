@@ -65,13 +65,22 @@ struct ShiftState {
     int conv_iter;     // base iteration at which it retired
 };
 
+// What one base iteration does to one shifted system, kept until the deferred update
+// of the shifted vectors applies it: x_k += alpha p_k, then p_k = zeta r + beta p_k.
+struct ShiftStep {
+    double alpha, zeta, beta;
+    int mode;          // 0: nothing, 1: the x_k step only (its last), 2: both
+    int pad_;
+};
+
 struct Ctl {
     int n_running;   // systems with SYS_RUNNING set; kernels of the inner loop exit when 0
     int pad0_;
     int nshift;      // multi-shift: shifts per RHS
     int nrhs;        // multi-shift: right-hand sides
     ShiftState *ms;  // multi-shift: [nshift][nrhs]
-    int pad_[10];
+    ShiftStep *steps;  // multi-shift: the deferred steps, [slot][nshift][nrhs]
+    int pad_[8];
 };
 
 enum FinOp {
@@ -253,12 +262,14 @@ __device__ __forceinline__ void finalize_one(int op, Ctl *ctl, SysState *st, dou
 
 // Multi-shift scalar steps for system j, by the whole block: thread 0 takes the
 // base system's step, then thread k < nshift that of shift k (the recurrences of
-// different shifts are independent).  Every thread of the block must call it;
-// sum is read in thread 0 only.
+// different shifts are independent).  OP_MS_BETA also leaves the iteration's step of
+// every shift in slot `slot` of ctl->steps, mode 0 where there is none, so a slot is
+// current after every iteration, whether or not the system still ran.  Every thread of
+// the block must call it; sum is read in thread 0 only.
 enum MsMode { MS_SKIP = 0, MS_RUN = 1, MS_FINISH = 2 };
 
 __device__ __forceinline__ void finalize_ms_block(int op, Ctl *ctl, SysState *st, int j,
-                                                  double sum) {
+                                                  double sum, int slot) {
     __shared__ int mode;
     __shared__ double sh_sum;
     SysState &s = st[j];
@@ -303,8 +314,13 @@ __device__ __forceinline__ void finalize_ms_block(int op, Ctl *ctl, SysState *st
     __syncthreads();  // also makes thread 0's state writes visible to the block
     const int m = mode;
     sum = sh_sum;
-    for (int k = threadIdx.x; k < ctl->nshift && m != MS_SKIP; k += blockDim.x) {
-        ShiftState &z = ctl->ms[k * ctl->nrhs + s.gid];
+    for (int k = threadIdx.x; k < ctl->nshift; k += blockDim.x) {
+        const int kj = k * ctl->nrhs + s.gid;
+        ShiftState &z = ctl->ms[kj];
+        if (m == MS_SKIP) {
+            if (op == OP_MS_BETA) ctl->steps[slot * ctl->nshift * ctl->nrhs + kj].mode = 0;
+            continue;
+        }
         if (op == OP_MS_ALPHA) {
             if (z.active == 2) z.active = 0;
             if (m != MS_RUN || z.active != 1) continue;
@@ -315,6 +331,8 @@ __device__ __forceinline__ void finalize_ms_block(int op, Ctl *ctl, SysState *st
             z.zeta_next = z.zeta * z.zeta_prev * s.alpha_prev / den;
             z.alpha = a * z.zeta_next / z.zeta;
         } else {
+            ShiftStep &step = ctl->steps[slot * ctl->nshift * ctl->nrhs + kj];
+            step.mode = 0;
             if (z.active != 1) continue;
             const double ratio = z.zeta_next / z.zeta;
             z.beta = s.beta * ratio * ratio;
@@ -325,6 +343,10 @@ __device__ __forceinline__ void finalize_ms_block(int op, Ctl *ctl, SysState *st
                 z.active = 2;
                 z.conv_iter = s.iter;
             }
+            step.alpha = z.alpha;
+            step.zeta = z.zeta;
+            step.beta = z.beta;
+            step.mode = (s.flags & SYS_RUNNING) && z.active == 1 ? 2 : 1;
         }
     }
 }
