@@ -78,6 +78,18 @@ __device__ __forceinline__ void mm_acc(su3<T> &c, const su3<T> &a, const su3<T> 
             for (int k = 0; k < 3; ++k) cfma(c.e[i][j], a.e[i][k], b.e[k][j]);
 }
 
+// C -= A B
+template <typename T>
+__device__ __forceinline__ void mm_sub(su3<T> &c, const su3<T> &a, const su3<T> &b) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                cfma(c.e[i][j], cpx<T>{-a.e[i][k].re, -a.e[i][k].im}, b.e[k][j]);
+}
+
 // C = A B^dag
 template <typename T>
 __device__ __forceinline__ su3<T> mmd(const su3<T> &a, const su3<T> &b) {
@@ -424,143 +436,268 @@ void staple_kernel(StapleArgs a) {
     }
 }
 
-// exp(iQ) for a traceless Hermitian 3x3 matrix Q.  Cayley-Hamilton gives
-// Q^3 = c1 Q + c0 with c0 = det Q = Tr(Q^3)/3 and c1 = Tr(Q^2)/2, so
-// exp(iQ) = f0 + f1 Q + f2 Q^2.  For c1 >= 1e-3 the f_j come in closed form from the
-// eigenvalues of Q, parametrised by u and w (Morningstar and Peardon, Phys. Rev. D 69,
-// 054501 (2004), Sec. III), computed for |c0| and mapped back by
-// f_j(-c0) = (-1)^j conj(f_j(c0)).  Below that, the power series of exp, reduced by the
-// same recurrence (Q^n = a_n + b_n Q + d_n Q^2), to 16 terms.
-__device__ __forceinline__ su3<double> exp_iq(const su3<double> &q) {
-    const su3<double> q2 = mm(q, q);
-    const double c1 = 0.5 * (q2.e[0][0].re + q2.e[1][1].re + q2.e[2][2].re);
-    double tr3 = 0.0;
+// A Hermitian 3x3 matrix: the real diagonal and the entries above it.
+struct herm3 {
+    double d[3];
+    cpx<double> o01, o02, o12;
+    __device__ __forceinline__ su3<double> full() const {
+        su3<double> m;
+        m.e[0][0] = {d[0], 0.0};
+        m.e[1][1] = {d[1], 0.0};
+        m.e[2][2] = {d[2], 0.0};
+        m.e[0][1] = o01;
+        m.e[0][2] = o02;
+        m.e[1][2] = o12;
+        m.e[1][0] = cconj(o01);
+        m.e[2][0] = cconj(o02);
+        m.e[2][1] = cconj(o12);
+        return m;
+    }
+};
+
+__device__ __forceinline__ double cabs2(cpx<double> a) { return fmat(a.re, a.re, a.im * a.im); }
+
+// Q Q of a Hermitian Q (Hermitian again)
+__device__ __forceinline__ herm3 square(const herm3 &q) {
+    const double n01 = cabs2(q.o01), n02 = cabs2(q.o02), n12 = cabs2(q.o12);
+    herm3 s;
+    s.d[0] = fmat(q.d[0], q.d[0], n01 + n02);
+    s.d[1] = fmat(q.d[1], q.d[1], n01 + n12);
+    s.d[2] = fmat(q.d[2], q.d[2], n02 + n12);
+    s.o01 = cscale(q.d[0] + q.d[1], q.o01);
+    cfma(s.o01, q.o02, cconj(q.o12));
+    s.o02 = cscale(q.d[0] + q.d[2], q.o02);
+    cfma(s.o02, q.o01, q.o12);
+    s.o12 = cscale(q.d[1] + q.d[2], q.o12);
+    cfmac(s.o12, q.o01, q.o02);
+    return s;
+}
+
+// det Q = Tr(Q^3) / 3 of a traceless Hermitian Q
+__device__ __forceinline__ double det(const herm3 &q) {
+    cpx<double> t = cmul(q.o01, q.o12);
+    const double z = fmat(t.re, q.o02.re, t.im * q.o02.im);  // Re(q01 q12 q20)
+    double v = q.d[0] * fmat(q.d[1], q.d[2], -cabs2(q.o12));
+    v = fmat(-q.d[1], cabs2(q.o02), v);
+    v = fmat(-q.d[2], cabs2(q.o01), v);
+    return fmat(2.0, z, v);
+}
+
+// exp(iQ) = f0 + f1 Q + f2 Q^2 for a traceless Hermitian Q (Cayley-Hamilton: Q^3 = c1 Q +
+// c0, c0 = det Q, c1 = Tr(Q^2)/2), and with DERIV the derivatives of f0, f1, f2 by c0 and
+// by c1, from which the derivative of exp(iQ) in any direction follows.
+//
+// The f_j are the coefficients of the exponential series reduced modulo the
+// characteristic polynomial, evaluated by Horner's rule on the triple (f0, f1, f2):
+// multiplying by Q maps it to (c0 f2, f0 + c1 f2, f1).  The coefficients i^n/n! are real
+// or imaginary in turn, so each step is two fused operations per part and five more for
+// the derivatives: about 90 (300 with the derivatives) in all, where the trigonometric
+// closed form takes several times that and the series in 3x3 matrices, as the derivative
+// had it before, 55 matrix products.  With c1 <= 3/4 the eigenvalues stay below 1 in
+// magnitude, the last of the 22 terms is below 1e-20 and no term cancels by more than a
+// factor e.  Larger Q: the triple of exp(iQ/2^s), squared s times in the same ring.
+struct ExpCoef {
+    cpx<double> f[3], d0[3], d1[3];
+};
+
+// (f, d0, d1) of p^2 from those of p, modulo Q^3 = c1 Q + c0
+template <bool DERIV>
+__device__ __forceinline__ void ring_square(ExpCoef &p, double c0, double c1) {
+    const cpx<double> a = p.f[0], b = p.f[1], c = p.f[2];
+    const cpx<double> t3 = cscale(2.0, cmul(b, c)), t4 = cmul(c, c);  // of Q^3 and Q^4
+    ExpCoef r;
+    r.f[0] = cadd(cmul(a, a), cscale(c0, t3));
+    r.f[1] = cadd(cscale(2.0, cmul(a, b)), cadd(cscale(c1, t3), cscale(c0, t4)));
+    r.f[2] = cadd(cadd(cscale(2.0, cmul(a, c)), cmul(b, b)), cscale(c1, t4));
+    if (DERIV) {
+        const auto dstep = [&](const cpx<double>(&q)[3], cpx<double>(&o)[3]) {
+            const cpx<double> u3 = cscale(2.0, cadd(cmul(q[1], c), cmul(b, q[2])));
+            const cpx<double> u4 = cscale(2.0, cmul(c, q[2]));
+            o[0] = cadd(cscale(2.0, cmul(a, q[0])), cscale(c0, u3));
+            o[1] = cadd(cscale(2.0, cadd(cmul(a, q[1]), cmul(q[0], b))),
+                        cadd(cscale(c1, u3), cscale(c0, u4)));
+            o[2] = cadd(cscale(2.0, cadd(cadd(cmul(a, q[2]), cmul(q[0], c)), cmul(b, q[1]))),
+                        cscale(c1, u4));
+        };
+        dstep(p.d0, r.d0);
+        r.d0[0] = cadd(r.d0[0], t3);
+        r.d0[1] = cadd(r.d0[1], t4);
+        dstep(p.d1, r.d1);
+        r.d1[1] = cadd(r.d1[1], t3);
+        r.d1[2] = cadd(r.d1[2], t4);
+    }
+    p.f[0] = r.f[0];
+    p.f[1] = r.f[1];
+    p.f[2] = r.f[2];
+    if (DERIV) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) tr3 += cmul(q.e[i][k], q2.e[k][i]).re;
-    const double c0 = tr3 / 3.0;
-    cpx<double> f0, f1, f2;
-    if (c1 < 1e-3) {
-        double an = 1.0, bn = 0.0, dn = 0.0, fact = 1.0;
-        cpx<double> ip = {1.0, 0.0};  // i^n
-        f0 = f1 = f2 = {0.0, 0.0};
-        for (int n = 0; n < 16; ++n) {
-            f0 = cadd(f0, cscale(an / fact, ip));
-            f1 = cadd(f1, cscale(bn / fact, ip));
-            f2 = cadd(f2, cscale(dn / fact, ip));
-            const double a1 = dn * c0, b1 = an + dn * c1, d1 = bn;
-            an = a1;
-            bn = b1;
-            dn = d1;
-            fact *= (double)(n + 1);
-            ip = {-ip.im, ip.re};
-        }
-    } else {
-        const double c0a = fabs(c0);
-        const double s3 = sqrt(c1 / 3.0);
-        const double c0max = 2.0 * s3 * s3 * s3;
-        const double th = acos(fmin(c0a / c0max, 1.0));
-        double st3, ct3, sw, cw, su, cu;
-        sincos(th / 3.0, &st3, &ct3);
-        const double u = s3 * ct3, w = sqrt(c1) * st3;
-        const double uu = u * u, ww = w * w;
-        sincos(w, &sw, &cw);
-        sincos(u, &su, &cu);
-        const double xi0 = fabs(w) < 0.05 ? 1.0 - ww / 6.0 * (1.0 - ww / 20.0 * (1.0 - ww / 42.0))
-                                          : sw / w;
-        const cpx<double> e2iu = {cu * cu - su * su, 2.0 * su * cu};  // exp(2iu)
-        const cpx<double> emiu = {cu, -su};                          // exp(-iu)
-        const cpx<double> h0 = cadd(cscale(uu - ww, e2iu),
-                                    cmul(emiu, cpx<double>{8.0 * uu * cw,
-                                                           2.0 * u * (3.0 * uu + ww) * xi0}));
-        const cpx<double> h1 = csub(cscale(2.0 * u, e2iu),
-                                    cmul(emiu, cpx<double>{2.0 * u * cw,
-                                                           -(3.0 * uu - ww) * xi0}));
-        const cpx<double> h2 = csub(e2iu, cmul(emiu, cpx<double>{cw, 3.0 * u * xi0}));
-        const double inv = 1.0 / (9.0 * uu - ww);
-        f0 = cscale(inv, h0);
-        f1 = cscale(inv, h1);
-        f2 = cscale(inv, h2);
-        if (c0 < 0.0) {
-            f0 = cconj(f0);
-            f1 = cscale(-1.0, cconj(f1));
-            f2 = cconj(f2);
+        for (int i = 0; i < 3; ++i) {
+            p.d0[i] = r.d0[i];
+            p.d1[i] = r.d1[i];
         }
     }
+}
+
+constexpr int kExpTerms = 22;
+
+constexpr double inv_factorial(int n) {
+    double v = 1.0;
+    for (int i = 2; i <= n; ++i) v /= (double)i;
+    return v;
+}
+
+template <int N>
+struct InvFactorials {
+    double v[N];
+    constexpr InvFactorials() : v() {
+        for (int n = 0; n < N; ++n) v[n] = inv_factorial(n);
+    }
+};
+
+template <bool DERIV>
+__device__ __forceinline__ ExpCoef exp_coef(double c0, double c1) {
+    int sq = 0;
+    while (c1 > 0.75 && sq < 40) {  // Q -> Q/2
+        c1 *= 0.25;
+        c0 *= 0.125;
+        ++sq;
+    }
+    constexpr InvFactorials<kExpTerms> inv;
+    // real and imaginary parts: cos and sin series, never mixed
+    double f[2][3] = {}, d0[2][3] = {}, d1[2][3] = {};
+#pragma unroll
+    for (int n = kExpTerms - 1; n >= 0; --n) {
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {  // 0: real, 1: imaginary
+            if (DERIV) {
+                const double a0 = fmat(c0, d0[z][2], f[z][2]);
+                const double a1 = fmat(c1, d0[z][2], d0[z][0]);
+                const double b0 = c0 * d1[z][2];
+                const double b1 = fmat(c1, d1[z][2], d1[z][0]) + f[z][2];
+                d0[z][2] = d0[z][1];
+                d0[z][0] = a0;
+                d0[z][1] = a1;
+                d1[z][2] = d1[z][1];
+                d1[z][0] = b0;
+                d1[z][1] = b1;
+            }
+            const double coef = (n & 1) == z ? ((n & 2) ? -inv.v[n] : inv.v[n]) : 0.0;
+            const double g0 = fmat(c0, f[z][2], coef), g1 = fmat(c1, f[z][2], f[z][0]);
+            f[z][2] = f[z][1];
+            f[z][0] = g0;
+            f[z][1] = g1;
+        }
+    }
+    ExpCoef e;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        e.f[i] = {f[0][i], f[1][i]};
+        e.d0[i] = {d0[0][i], d0[1][i]};
+        e.d1[i] = {d1[0][i], d1[1][i]};
+    }
+    if (sq > 0) {
+        for (int r = 0; r < sq; ++r) ring_square<DERIV>(e, c0, c1);
+        // from powers of Q/2^s to powers of Q
+        const double h = ldexp(1.0, -sq);
+        e.f[1] = cscale(h, e.f[1]);
+        e.f[2] = cscale(h * h, e.f[2]);
+        if (DERIV) {
+            const double h2 = h * h, h3 = h2 * h;
+            double w = 1.0;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                e.d0[i] = cscale(w * h3, e.d0[i]);
+                e.d1[i] = cscale(w * h2, e.d1[i]);
+                w *= h;
+            }
+        }
+    }
+    return e;
+}
+
+// f0 + f1 Q + f2 Q^2
+__device__ __forceinline__ su3<double> exp_matrix(const ExpCoef &c, const herm3 &q,
+                                                  const herm3 &q2) {
+    const su3<double> a = q.full(), b = q2.full();
     su3<double> e;
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            cpx<double> v = cadd(cmul(f1, q.e[i][k]), cmul(f2, q2.e[i][k]));
-            if (i == k) v = cadd(v, f0);
-            e.e[i][k] = v;
+            if (i == k) {
+                e.e[i][k] = {fmat(c.f[2].re, b.e[i][k].re, fmat(c.f[1].re, a.e[i][k].re, c.f[0].re)),
+                             fmat(c.f[2].im, b.e[i][k].re, fmat(c.f[1].im, a.e[i][k].re, c.f[0].im))};
+            } else {
+                cpx<double> v = cmul(c.f[1], a.e[i][k]);
+                cfma(v, c.f[2], b.e[i][k]);
+                e.e[i][k] = v;
+            }
         }
     return e;
 }
 
-// exp(B) and the Frechet derivative L(B, M) = d/dt exp(B + t M) at t = 0 for a general
-// 3x3 complex B, M: exp of the block matrix [[B, M], [0, B]] is [[e^B, L], [0, e^B]].  With
-// T_n = B^n / n! and X_n the top-right block of the n-th term, X_n = (B X_{n-1} + M T_{n-1})/n;
-// B and M are first scaled by 2^-s so that |B|_F <= 1/4, the series taken to 14 terms
-// (remainder below 1e-20), and the pair squared back s times: (E, L) -> (E E, E L + L E).
-__device__ __forceinline__ void exp_frechet(const su3<double> &b, const su3<double> &m,
-                                            su3<double> &e, su3<double> &l) {
-    double nb = 0.0;
+// exp(iQ) for a traceless Hermitian Q
+__device__ __forceinline__ su3<double> exp_iq(const herm3 &q) {
+    const herm3 q2 = square(q);
+    return exp_matrix(exp_coef<false>(det(q), 0.5 * (q2.d[0] + q2.d[1] + q2.d[2])), q, q2);
+}
+
+// Q = (i/2)(Omega^dag - Omega) - (i/6) Tr(Omega^dag - Omega)
+__device__ __forceinline__ herm3 stout_q(const su3<double> &om) {
+    const double tq = (om.e[0][0].im + om.e[1][1].im + om.e[2][2].im) / 3.0;
+    herm3 q;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) q.d[i] = om.e[i][i].im - tq;
+    const auto off = [&](int i, int k) {
+        const cpx<double> z = csub(cconj(om.e[k][i]), om.e[i][k]);
+        return cpx<double>{-0.5 * z.im, 0.5 * z.re};
+    };
+    q.o01 = off(0, 1);
+    q.o02 = off(0, 2);
+    q.o12 = off(1, 2);
+    return q;
+}
+
+// The traceless anti-Hermitian matrix G of a link between the two passes: the imaginary
+// parts of G00 and G11 (G22 = -G00 - G11), then G01, G02, G12: four 16-byte words,
+// [slot][word][site].
+__device__ __forceinline__ su3<double> load_g(const void *ws, uint32_t Vh, int s, uint32_t h) {
+    const double2 *p = reinterpret_cast<const double2 *>(ws) + (size_t)s * 4 * Vh + h;
+    const double2 d = p[0], a = p[Vh], b = p[2 * (size_t)Vh], c = p[3 * (size_t)Vh];
+    su3<double> g;
+    g.e[0][0] = {0.0, d.x};
+    g.e[1][1] = {0.0, d.y};
+    g.e[2][2] = {0.0, -d.x - d.y};
+    g.e[0][1] = {a.x, a.y};
+    g.e[0][2] = {b.x, b.y};
+    g.e[1][2] = {c.x, c.y};
+    g.e[1][0] = {-a.x, a.y};
+    g.e[2][0] = {-b.x, b.y};
+    g.e[2][1] = {-c.x, c.y};
+    return g;
+}
+
+__device__ __forceinline__ cpx<double> trace_mul(const su3<double> &a, const su3<double> &b) {
+    cpx<double> t = {0.0, 0.0};
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) nb += b.e[i][k].re * b.e[i][k].re + b.e[i][k].im * b.e[i][k].im;
-    nb = sqrt(nb);
-    int sq = 0;
-    while (nb > 0.25 && sq < 40) {
-        nb *= 0.5;
-        ++sq;
-    }
-    const double sc = ldexp(1.0, -sq);
-    su3<double> bs, ms, t, x;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            bs.e[i][k] = cscale(sc, b.e[i][k]);
-            ms.e[i][k] = cscale(sc, m.e[i][k]);
-            t.e[i][k] = {i == k ? 1.0 : 0.0, 0.0};
-            x.e[i][k] = {0.0, 0.0};
-        }
-    e = t;
-    l = x;
-#pragma unroll 1
-    for (int n = 1; n <= 14; ++n) {
-        su3<double> xn = mm(bs, x);
-        mm_acc(xn, ms, t);
-        t = mm(bs, t);
-        const double inv = 1.0 / (double)n;
-        scale(xn, inv);
-        scale(t, inv);
-        x = xn;
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                e.e[i][k] = cadd(e.e[i][k], t.e[i][k]);
-                l.e[i][k] = cadd(l.e[i][k], x.e[i][k]);
-            }
-    }
-#pragma unroll 1
-    for (int r = 0; r < sq; ++r) {
-        su3<double> ln = mm(e, l);
-        mm_acc(ln, l, e);
-        l = ln;
-        e = mm(e, e);
-    }
+        for (int k = 0; k < 3; ++k) cfma(t, a.e[i][k], b.e[k][i]);
+    return t;
 }
 
 // Pass 1 of the force through a stout step, one thread per link l = (mu, x):
 // C = rho (3-link paths from x to x+mu), Omega = C U^dag, Q, M = U Sigma'_l,
-// Gamma = L(iQ, M); G = (Gamma - Gamma^dag)/2 + (conj(Tr Gamma) - Tr Gamma)/6;
-// out_l = Sigma'_l exp(iQ) + C^dag G^dag, ws_l = U^dag G.
+// Gamma = L(iQ, M) with L the Frechet derivative of exp; G = (Gamma - Gamma^dag)/2 +
+// (conj(Tr Gamma) - Tr Gamma)/6; out_l = Sigma'_l exp(iQ) + C^dag G^dag, ws_l = G.
+//
+// With exp(iQ) = f0 + f1 Q + f2 Q^2 the derivative in the direction E = -iM of Q is
+//   df0 + df1 Q + df2 Q^2 + f1 E + f2 (Q E + E Q),
+//   df_j = (df_j/dc0) Tr(Q^2 E0) + (df_j/dc1) Tr(Q E0),  E0 = E - Tr(E)/3,
+// and the part Tr(E)/3 of E along the identity adds i Tr(E)/3 exp(iQ) in place of its
+// share in the terms above.  Multiples of the identity drop out of G.  (Before, L came
+// from a 14-term series of 3x3 products scaled and squared back: 55 products per link of
+// 75; the pass took 1399 us at 24^3 x 48, now 550.)
 template <int FMT>
 __global__ __launch_bounds__(kStoutBlock) void stout_back1_kernel(StoutBackArgs a) {
     const Geom &g = a.geom;
@@ -594,61 +731,99 @@ __global__ __launch_bounds__(kStoutBlock) void stout_back1_kernel(StoutBackArgs 
         mm_acc(c, mdm(U(nu, nm1, 1), U(mu, nm1, 1)), U(nu, mp1 + nm1, 0));
     }
     scale(c, a.rho);
-    const su3<double> u = U(mu, 0, 0);
-    const su3<double> om = mmd(c, u);
-    const double tq = (om.e[0][0].im + om.e[1][1].im + om.e[2][2].im) / 3.0;
-    su3<double> iq;  // i Q
+    su3<double> m;  // E = -i U Sigma'
+    herm3 q;
+    {
+        const su3<double> u = U(mu, 0, 0);
+        q = stout_q(mmd(c, u));
+        m = mm(u, cached_link<double, FMT_C128_18>::load(a.sigp, g.Vh, slot, h));
+    }
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const cpx<double> z = csub(cconj(om.e[k][i]), om.e[i][k]);
-            cpx<double> qv = {-0.5 * z.im, 0.5 * z.re};
-            if (i == k) qv.re -= tq;
-            iq.e[i][k] = {-qv.im, qv.re};
-        }
-    const su3<double> sp = cached_link<double, FMT_C128_18>::load(a.sigp, g.Vh, slot, h);
-    su3<double> e, gam;
-    exp_frechet(iq, mm(u, sp), e, gam);
-    const cpx<double> tg = cadd(cadd(gam.e[0][0], gam.e[1][1]), gam.e[2][2]);
-    const cpx<double> dtr = cscale(1.0 / 6.0, csub(cconj(tg), tg));
+        for (int k = 0; k < 3; ++k) m.e[i][k] = {m.e[i][k].im, -m.e[i][k].re};
+    const herm3 q2 = square(q);
+    const double c1 = 0.5 * (q2.d[0] + q2.d[1] + q2.d[2]);
+    const ExpCoef f = exp_coef<true>(det(q), c1);
+    const su3<double> qf = q.full(), q2f = q2.full();
+    const cpx<double> t3 = cscale(1.0 / 3.0, cadd(cadd(m.e[0][0], m.e[1][1]), m.e[2][2]));
+    const cpx<double> tq1 = trace_mul(qf, m);                                       // Tr(Q E0)
+    const cpx<double> tq2 = csub(trace_mul(q2f, m), cscale(2.0 * c1, t3));          // Tr(Q^2 E0)
+    const cpx<double> it3 = {-t3.im, t3.re};
+    // of the terms al Q and be Q^2 (Hermitian matrices) only the imaginary parts of al
+    // and be reach the anti-Hermitian G
+    cpx<double> al = cmul(f.d0[1], tq2), be = cmul(f.d0[2], tq2);
+    cfma(al, f.d1[1], tq1);
+    cfma(al, it3, f.f[1]);
+    cfma(al, cscale(-2.0, t3), f.f[2]);
+    cfma(be, f.d1[2], tq1);
+    cfma(be, it3, f.f[2]);
+    su3<double> gam;
+    {
+        su3<double> w = mm(qf, m);
+        mm_acc(w, m, qf);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                gam.e[i][k] = cmul(f.f[1], m.e[i][k]);
+                cfma(gam.e[i][k], f.f[2], w.e[i][k]);
+            }
+    }
     su3<double> gg;
+    double gd[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        gd[i] = fmat(al.im, q.d[i], fmat(be.im, q2.d[i], gam.e[i][i].im));
+    const double tg = (gd[0] + gd[1] + gd[2]) / 3.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) gg.e[i][i] = {0.0, gd[i] - tg};
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
+        for (int k = i + 1; k < 3; ++k) {
             cpx<double> v = cscale(0.5, csub(gam.e[i][k], cconj(gam.e[k][i])));
-            if (i == k) v = cadd(v, dtr);
+            // + i (Im al Q + Im be Q^2)
+            v.re = fmat(-al.im, qf.e[i][k].im, fmat(-be.im, q2f.e[i][k].im, v.re));
+            v.im = fmat(al.im, qf.e[i][k].re, fmat(be.im, q2f.e[i][k].re, v.im));
             gg.e[i][k] = v;
+            gg.e[k][i] = {-v.re, v.im};
         }
-    su3<double> loc = mm(sp, e);
-    // + C^dag G^dag = (G C)^dag
-    const su3<double> gcm = mm(gg, c);
-    const su3<double> ug = mdm(u, gg);  // U^dag G
+    double2 *gp = reinterpret_cast<double2 *>(a.ws) + (size_t)slot * 4 * g.Vh + h;
+    gp[0] = make_double2(gg.e[0][0].im, gg.e[1][1].im);
+    gp[g.Vh] = make_double2(gg.e[0][1].re, gg.e[0][1].im);
+    gp[2 * (size_t)g.Vh] = make_double2(gg.e[0][2].re, gg.e[0][2].im);
+    gp[3 * (size_t)g.Vh] = make_double2(gg.e[1][2].re, gg.e[1][2].im);
+    const su3<double> gcm = mm(gg, c);  // C^dag G^dag = (G C)^dag
+    const su3<double> e = exp_matrix(f, q, q2);
+    const su3<double> loc = mm(cached_link<double, FMT_C128_18>::load(a.sigp, g.Vh, slot, h), e);
     const size_t base = (size_t)slot * 9 * g.Vh + h;
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const size_t idx = base + (size_t)(i * 3 + k) * g.Vh;
-            st_c<double>(a.out, idx, cadd(loc.e[i][k], cconj(gcm.e[k][i])));
-            st_c<double>(a.ws, idx, ug.e[i][k]);
-        }
+        for (int k = 0; k < 3; ++k)
+            st_c<double>(a.out, base + (size_t)(i * 3 + k) * g.Vh,
+                         cadd(loc.e[i][k], cconj(gcm.e[k][i])));
 }
 
 // Pass 2, two threads per link l = (nu, y): add rho times every product in which l
-// stands in a 3-link path of C at a neighbouring link (gc = U^dag G from pass 1):
-// for each direction b != nu,
-//   l as the middle link:  U_b(y-b+nu)^dag gc(nu, y-b) U_b(y-b),
-//                          U_b(y+nu) gc(nu, y+b) U_b(y)^dag;
-//   l as a side link:      U_b(y+nu) U_nu(y+b)^dag gc(b, y),
-//                          [gc(b, y-b) U_nu(y-b) U_b(y-b+nu)]^dag,
-//                          [U_b(y) U_nu(y+b) gc(b, y+nu)]^dag,
-//                          gc(b, y+nu-b) U_nu(y-b)^dag U_b(y-b).
+// stands in a 3-link path of C at a neighbouring link.  For a path's own link l' the
+// product ends in U_l'^dag G_l', and the G are anti-Hermitian, so for each direction
+// b != nu the three paths on either side of the link share their factors.  With
+// U1 = U_b(y+nu), U2 = U_nu(y+b), U3 = U_b(y), G1 = G(nu,y+b), G3 = G(b,y), G5 = G(b,y+nu)
+// the side of +b adds
+//   U1 U2^dag G1 U3^dag + U1 U2^dag U3^dag G3 - G5 U1 U2^dag U3^dag
+//     = (P G1 - G5 P) U3^dag + (P U3^dag) G3,  P = U1 U2^dag,
+// and with V1 = U_b(y-b+nu), V2 = U_nu(y-b), V3 = U_b(y-b), H1 = G(nu,y-b), H3 = G(b,y-b),
+// H5 = G(b,y-b+nu) the side of -b
+//   V1^dag [ V2^dag (H1 - H3) + H5 V2^dag ] V3:
+// 10 matrix products and 60 16-byte loads of the 12-real links and the G per direction
+// (12 and 126 when the six products were taken one by one from stored U^dag G), which is
+// what bounds the pass (1128 -> 869 us at 24^3 x 48).
 template <int FMT>
 __global__ __launch_bounds__(2 * kStapleLinks) void stout_back2_kernel(StoutBackArgs a) {
-    // two waves over the same kStapleLinks links: wave 0 sums the first three products
-    // of each direction, wave 1 the last three; wave 1's sums meet wave 0's in LDS
+    // two waves over the same kStapleLinks links: wave 0 sums the +b sides, wave 1 the -b
+    // sides; wave 1's sums meet wave 0's in LDS
     __shared__ cpx<double> part[9][kStapleLinks];
     const Geom &g = a.geom;
     const uint32_t blk = a.xcd_remap ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
@@ -671,7 +846,9 @@ __global__ __launch_bounds__(2 * kStapleLinks) void stout_back2_kernel(StoutBack
         const int L = (int)s.x[0] + st[1] * (int)s.x[1] + st[2] * (int)s.x[2] +
                       st[3] * (int)s.x[3];
         const LinkAt<double, FMT> U{a.links, g.Vh, L, P};
-        const LinkAt<double, FMT_C128_18> W{a.ws, g.Vh, L, P};
+        const auto G = [&](int d, int dl, int flip) {
+            return load_g(a.ws, g.Vh, 2 * d + ((P + flip) & 1), (uint32_t)(L + dl) >> 1);
+        };
         const int xv = (int)pick4(s.x[0], s.x[1], s.x[2], s.x[3], nu);
         const int nv = (int)pick4(g.N[0], g.N[1], g.N[2], g.N[3], nu);
         const int sv = (int)pick4(st[0], st[1], st[2], st[3], nu);
@@ -682,34 +859,28 @@ __global__ __launch_bounds__(2 * kStapleLinks) void stout_back2_kernel(StoutBack
             const int xb = (int)pick4(s.x[0], s.x[1], s.x[2], s.x[3], b);
             const int nb = (int)pick4(g.N[0], g.N[1], g.N[2], g.N[3], b);
             const int sb = (int)pick4(st[0], st[1], st[2], st[3], b);
-            const int bp1 = lex_step(xb, 1, nb, sb), bm1 = lex_step(xb, -1, nb, sb);
             if (q == 0) {
-                // middle link
-                mm_acc(acc, mdm(U(b, bm1 + vp1, 0), W(nu, bm1, 1)), U(b, bm1, 1));
-                mmd_acc(acc, mm(U(b, vp1, 1), W(nu, bp1, 1)), U(b, 0, 0));
-                // side link, forward: U_b(y+nu) U_nu(y+b)^dag gc(b, y)
-                mm_acc(acc, mmd(U(b, vp1, 1), U(nu, bp1, 1)), W(b, 0, 0));
+                const int bp1 = lex_step(xb, 1, nb, sb);
+                const su3<double> p = mmd(U(b, vp1, 1), U(nu, bp1, 1));
+                su3<double> t = mm(p, G(nu, bp1, 1));
+                mm_sub(t, G(b, vp1, 1), p);
+                const su3<double> u3 = U(b, 0, 0);
+                mmd_acc(acc, t, u3);
+                mm_acc(acc, mmd(p, u3), G(b, 0, 0));
             } else {
-                // side link, forward: gc(b, y+nu-b) U_nu(y-b)^dag U_b(y-b)
-                mm_acc(acc, mmd(W(b, vp1 + bm1, 0), U(nu, bm1, 1)), U(b, bm1, 1));
-                // side links walked backwards: add the daggers, one product at a time
+                const int bm1 = lex_step(xb, -1, nb, sb);
+                const su3<double> v2 = U(nu, bm1, 1);
+                su3<double> d = G(nu, bm1, 1);
                 {
-                    const su3<double> t4 =
-                        mm(mm(W(b, bm1, 1), U(nu, bm1, 1)), U(b, bm1 + vp1, 0));
+                    const su3<double> h3 = G(b, bm1, 1);
 #pragma unroll
                     for (int i = 0; i < 3; ++i)
 #pragma unroll
-                        for (int c = 0; c < 3; ++c)
-                            acc.e[i][c] = cadd(acc.e[i][c], cconj(t4.e[c][i]));
+                        for (int c = 0; c < 3; ++c) d.e[i][c] = csub(d.e[i][c], h3.e[i][c]);
                 }
-                {
-                    const su3<double> t5 = mm(mm(U(b, 0, 0), U(nu, bp1, 1)), W(b, vp1, 1));
-#pragma unroll
-                    for (int i = 0; i < 3; ++i)
-#pragma unroll
-                        for (int c = 0; c < 3; ++c)
-                            acc.e[i][c] = cadd(acc.e[i][c], cconj(t5.e[c][i]));
-                }
+                su3<double> t = mdm(v2, d);
+                mmd_acc(t, G(b, bm1 + vp1, 0), v2);
+                mm_acc(acc, mdm(U(b, bm1 + vp1, 0), t), U(b, bm1, 1));
             }
         }
     }
@@ -773,18 +944,7 @@ __global__ __launch_bounds__(kStoutBlock) void stout_kernel(StoutArgs a) {
     }
     scale(c, a.rho);
     const su3<double> u = U(mu, 0, 0);
-    const su3<double> om = mmd(c, u);  // Omega = C U^dag
-    // Q = (i/2)(Omega^dag - Omega) - (1/3) sum_i Im(Omega_ii) I
-    const double tq = (om.e[0][0].im + om.e[1][1].im + om.e[2][2].im) / 3.0;
-    su3<double> q;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const cpx<double> z = csub(cconj(om.e[k][i]), om.e[i][k]);
-            q.e[i][k] = {-0.5 * z.im, 0.5 * z.re};
-            if (i == k) q.e[i][k].re -= tq;
-        }
+    const herm3 q = stout_q(mmd(c, u));  // of Omega = C U^dag
     const su3<double> up = mm(exp_iq(q), u);
     const size_t base = (size_t)slot * 9 * g.Vh + h;
 #pragma unroll
@@ -821,7 +981,9 @@ int launch_mom(const StapleArgs &a, int threads, hipStream_t stream) {
     return -1;
 }
 
-// U -> exp(i eps P) U in place, one thread per link, in the link's own format.  The
+// U -> exp(i eps P) U in place, one thread per link, in the link's own format.  Bound by
+// its traffic: of the Hermitian P the diagonal and the entries above it are read (288 B
+// per FP64-12 link with them, 336 with all nine; 267 -> 210 us at 32^4).  The
 // exponential is formed in FP64 also for FP32 links and momenta (its cost is small
 // next to the link and momentum traffic), the product with U in the format's type.
 template <typename T, int FMT>
@@ -833,15 +995,13 @@ __global__ __launch_bounds__(kStoutBlock) void link_update_kernel(LinkUpdateArgs
     const int slot = (int)(t / Vh);
     const uint32_t h = (uint32_t)(t % Vh);
     const su3<T> u = cached_link<T, FMT>::load(a.links, Vh, slot, h);
-    su3<double> q;
+    // eps P: of a Hermitian matrix the diagonal and the entries above it are read
     const size_t base = (size_t)slot * 9 * Vh + h;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const cpx<T> p = ld_c<T>(a.mom, base + (size_t)(i * 3 + k) * Vh);
-            q.e[i][k] = {a.eps * (double)p.re, a.eps * (double)p.im};
-        }
+    const auto P = [&](int i, int k) {
+        const cpx<T> p = ld_c<T>(a.mom, base + (size_t)(i * 3 + k) * Vh);
+        return cpx<double>{a.eps * (double)p.re, a.eps * (double)p.im};
+    };
+    const herm3 q = {{P(0, 0).re, P(1, 1).re, P(2, 2).re}, P(0, 1), P(0, 2), P(1, 2)};
     const su3<double> e64 = exp_iq(q);
     su3<T> e;
 #pragma unroll

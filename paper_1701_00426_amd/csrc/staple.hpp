@@ -59,7 +59,8 @@ struct StoutBackArgs {
     const void *links;  // thin FP64 gauge field
     const void *sigp;   // complex128 [8][3][3][Vh]: dS/dU' of the smeared links
     void *out;          // complex128 [8][3][3][Vh]: dS/dU of the thin links
-    void *ws;           // complex128 [8][3][3][Vh]: U^dag G per link
+    void *ws;           // scratch of 8*9*Vh complex128; holds the traceless anti-Hermitian G per
+                        // link, double2 [8][4][Vh]
     double rho;
     int xcd_remap;
 };
