@@ -36,7 +36,7 @@ int g_xcd_remap = 1;
 int g_sites_per_thread = 1;
 int g_stage_neighbours = 0;
 int g_threads_per_site = 0;  // 0: by format and fields
-int g_staple_threads = 0;    // 0: by format
+int g_staple_threads = 0;    // 0: by format and size
 int g_pencil_tile = 0;       // tile shape of the pencil order (pencil.hpp)
 int g_fields_per_launch = 0; // 0: the autotuned choice for the lattice and format, else 8
 int g_layer_group = 0;       // 0: half-index order; G: layer order, G x3 planes per group
@@ -1893,7 +1893,7 @@ int gauge_staples(const stg_lattice *lat, const stg_gauge *gauge, double c0, dou
     a.c0 = c0;
     a.c1 = c1;
     a.xcd_remap = g_xcd_remap;
-    const int threads = g_staple_threads ? g_staple_threads : staple_default_threads(gauge->fmt);
+    const int threads = g_staple_threads ? g_staple_threads : staple_default_threads(gauge->fmt, g.Vh);
     if (launch_staples(a, gauge->fmt, threads, (hipStream_t)stream))
         return invalid("unknown link format");
     HIP_TRY(hipGetLastError());
@@ -1988,7 +1988,7 @@ int gauge_momentum_update(const stg_lattice *lat, const stg_gauge *gauge, double
     a.c1 = c1;
     a.kmom = eps * beta / 3.0;
     a.xcd_remap = g_xcd_remap;
-    const int threads = g_staple_threads ? g_staple_threads : staple_default_threads(gauge->fmt);
+    const int threads = g_staple_threads ? g_staple_threads : staple_default_threads(gauge->fmt, g.Vh);
     if (launch_momentum(a, gauge->fmt, threads, (hipStream_t)stream))
         return invalid("unsupported link format for the momentum update");
     HIP_TRY(hipGetLastError());

@@ -17,14 +17,15 @@
 // neighbourhood is mostly in the XCD's L2.  Neighbour half indices come from
 // coordinate arithmetic (no index tables).  The 8 paths of each side (above /
 // below the link) share their factors:
-//   above:  A = U_nu(x+mu), W = U_mu(x+nu)^dag U_nu(x)^dag,
-//           D = U_mu(x-mu+nu)^dag U_nu(x-mu)^dag U_mu(x-mu),
-//           T = U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag,
-//           E = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag,
-//   1x1: A W;  1x2: E W (long side forward), A U_mu(x+nu)^dag D (long side
-//   backward), A T U_nu(x)^dag (long side along nu), so the side contributes
-//           A [c0 W + c1 (U_mu(x+nu)^dag D + T U_nu(x)^dag)] + c1 E W,
-// 11 SU(3) products instead of 14 taken path by path; below the link likewise
+//   above:  X = U_nu(x+mu) U_mu(x+nu)^dag,
+//           Y = U_nu(x+mu) U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag,
+//           Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag U_mu(x+nu)^dag,
+//           W = X U_mu(x-mu+nu)^dag U_nu(x-mu)^dag,
+//   1x1: X U_nu(x)^dag;  1x2: Y U_nu(x)^dag (long side along nu), Z U_nu(x)^dag (long
+//   side forward), W U_mu(x-mu) (long side backward), so the side contributes
+//           [c0 X + c1 (Y + Z)] U_nu(x)^dag + c1 W U_mu(x-mu),
+// 11 SU(3) products instead of 14 taken path by path, 9 of them (X, Y, Z and W) chains of
+// links that need two rows only; below the link likewise
 // with nu -> -nu.  Products accumulate in the arithmetic type of the format
 // (FP64 for complex128 links, FP32 for the 12-real FP32 / BF16 ones).
 //
@@ -294,11 +295,189 @@ struct LinkAt {
     }
 };
 
-// The 1x1 and 1x2 paths on the +nu side of the link: A [c0 W + c1 (U_mu(x+nu)^dag D +
-// T U_nu(x)^dag)] + c1 E W.  mp1 .. np2: lexicographic displacements of x +- mu, x + 2mu,
-// x +- nu, x + 2nu (periodic).
+// The first R rows of a 3x3 matrix.  A product of SU(3) links is SU(3), so two of its
+// rows give the third: chains of links are multiplied on R = 2 rows (72 fused operations
+// instead of 108, 24 registers of FP64 instead of 36) and completed at the end.  R = 3 for
+// BF16-12 links, whose rows are rounded to 8 bits and not orthonormal to FP32 (FP64-18
+// links, any matrices, take side_*_full).  32^4, staples: FP64-12 1917 -> 1590 us, FP32-12
+// 1080 -> 787, BF16-12 884 -> 857; the FP64 kernel before issued 11 000 vector
+// instructions per link and kept the vector units 65 % busy.
+template <typename T, int R>
+struct rows {
+    cpx<T> e[R][3];
+};
+
+template <int FMT>
+constexpr int chain_rows() {
+    return FMT == FMT_BF16_12 ? 3 : 2;
+}
+
+template <typename T, int R>
+__device__ __forceinline__ rows<T, R> rmul(const rows<T, R> &a, const su3<T> &b) {  // A B
+    rows<T, R> c;
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            cpx<T> t = cmul(a.e[i][0], b.e[0][j]);
+            cfma(t, a.e[i][1], b.e[1][j]);
+            cfma(t, a.e[i][2], b.e[2][j]);
+            c.e[i][j] = t;
+        }
+    return c;
+}
+
+template <typename T, int R>
+__device__ __forceinline__ rows<T, R> rmuld(const rows<T, R> &a, const su3<T> &b) {  // A B^dag
+    rows<T, R> c;
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            cpx<T> t = cmulc(b.e[j][0], a.e[i][0]);
+            cfmac(t, b.e[j][1], a.e[i][1]);
+            cfmac(t, b.e[j][2], a.e[i][2]);
+            c.e[i][j] = t;
+        }
+    return c;
+}
+
+template <typename T, int R>
+__device__ __forceinline__ rows<T, R> rows_of(const su3<T> &u) {
+    rows<T, R> r;
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) r.e[i][j] = u.e[i][j];
+    return r;
+}
+
+template <typename T, int R>
+__device__ __forceinline__ rows<T, R> rows_of_dag(const su3<T> &u) {
+    rows<T, R> r;
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) r.e[i][j] = cconj(u.e[j][i]);
+    return r;
+}
+
+// g += w times the matrix of r (R = 2: with its third row, conj(row 0 x row 1))
+template <typename T, int R>
+__device__ __forceinline__ void add_rows(su3<T> &g, T w, const rows<T, R> &r) {
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            g.e[i][j].re = fmat(w, r.e[i][j].re, g.e[i][j].re);
+            g.e[i][j].im = fmat(w, r.e[i][j].im, g.e[i][j].im);
+        }
+    if constexpr (R == 2) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const cpx<T> a = r.e[0][(j + 1) % 3], b = r.e[1][(j + 2) % 3];
+            const cpx<T> c = r.e[0][(j + 2) % 3], d = r.e[1][(j + 1) % 3];
+            T re = a.re * b.re, im = -a.re * b.im;  // conj(a b - c d)
+            re = fmat(-a.im, b.im, re);
+            im = fmat(-a.im, b.re, im);
+            re = fmat(-c.re, d.re, re);
+            im = fmat(c.re, d.im, im);
+            re = fmat(c.im, d.im, re);
+            im = fmat(c.im, d.re, im);
+            g.e[2][j].re = fmat(w, re, g.e[2][j].re);
+            g.e[2][j].im = fmat(w, im, g.e[2][j].im);
+        }
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void set_zero(su3<T> &c) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) c.e[i][j] = {T(0), T(0)};
+}
+
+// The four paths on the +nu side of the link (header): acc += [c0 X + c1 (Y + Z)] C^dag,
+// and the path whose long side runs backward, X U_mu(x-mu+nu)^dag U_nu(x-mu)^dag U_mu(x-mu):
+// with BACK its last factor, common to all sides, is left to the caller and the product
+// before it is added to back, else c1 times the path is added to acc.
+// mp1 .. np2: lexicographic displacements of x +- mu, x + 2mu, x +- nu, x + 2nu (periodic).
+template <typename T, int FMT, bool BACK>
+__device__ __forceinline__ void side_above(su3<T> &acc, su3<T> &back, const LinkAt<T, FMT> &U,
+                                           int mu, int nu, int mp1, int mm1, int mp2, int np1,
+                                           int np2, T c0, T c1) {
+    constexpr int R = chain_rows<FMT>();
+    su3<T> g;
+    set_zero(g);
+    rows<T, R> a;
+    {
+        const su3<T> b = U(mu, np1, 1);
+        // Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag U_mu(x+nu)^dag
+        a = rmul(rows_of<T, R>(U(mu, mp1, 1)), U(nu, mp2, 0));
+        a = rmuld(a, U(mu, mp1 + np1, 0));
+        a = rmuld(a, b);
+        add_rows(g, c1, a);
+        // X = U_nu(x+mu) U_mu(x+nu)^dag
+        a = rows_of<T, R>(U(nu, mp1, 1));
+        rows<T, R> x = rmuld(a, b);
+        add_rows(g, c0, x);
+        x = rmuld(x, U(mu, mm1 + np1, 0));
+        x = rmuld(x, U(nu, mm1, 1));
+        if constexpr (BACK)
+            add_rows(back, T(1), x);
+        else
+            add_rows(acc, c1, rmul(x, U(mu, mm1, 1)));
+    }
+    // Y = U_nu(x+mu) U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag
+    a = rmul(a, U(nu, mp1 + np1, 0));
+    a = rmuld(a, U(mu, np2, 0));
+    a = rmuld(a, U(nu, np1, 1));
+    add_rows(g, c1, a);
+    mmd_acc(acc, g, U(nu, 0, 0));
+}
+
+// The same on the -nu side, every U_nu step reversed.
+template <typename T, int FMT, bool BACK>
+__device__ __forceinline__ void side_below(su3<T> &acc, su3<T> &back, const LinkAt<T, FMT> &U,
+                                           int mu, int nu, int mp1, int mm1, int mp2, int nm1,
+                                           int nm2, T c0, T c1) {
+    constexpr int R = chain_rows<FMT>();
+    su3<T> g;
+    set_zero(g);
+    rows<T, R> a;
+    {
+        const su3<T> b = U(mu, nm1, 1);
+        a = rmuld(rows_of<T, R>(U(mu, mp1, 1)), U(nu, mp2 + nm1, 1));
+        a = rmuld(a, U(mu, mp1 + nm1, 0));
+        a = rmuld(a, b);
+        add_rows(g, c1, a);
+        a = rows_of_dag<T, R>(U(nu, mp1 + nm1, 0));
+        rows<T, R> x = rmuld(a, b);
+        add_rows(g, c0, x);
+        x = rmuld(x, U(mu, mm1 + nm1, 0));
+        x = rmul(x, U(nu, mm1 + nm1, 0));
+        if constexpr (BACK)
+            add_rows(back, T(1), x);
+        else
+            add_rows(acc, c1, rmul(x, U(mu, mm1, 1)));
+    }
+    a = rmuld(a, U(nu, mp1 + nm2, 1));
+    a = rmuld(a, U(mu, nm2, 0));
+    a = rmul(a, U(nu, nm2, 0));
+    add_rows(g, c1, a);
+    mm_acc(acc, g, U(nu, nm1, 1));
+}
+
+// The same sums for FP64-18 links, any matrices: chains of three rows in FP64 hold so many
+// registers that they spill (32^4: 2250 us against 2041 us of this form), so there the
+// sides are summed as A [c0 W + c1 (U_mu(x+nu)^dag D + T U_nu(x)^dag)] + c1 E W with
+//   A = U_nu(x+mu), W = U_mu(x+nu)^dag U_nu(x)^dag,
+//   D = U_mu(x-mu+nu)^dag U_nu(x-mu)^dag U_mu(x-mu),
+//   T = U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag,
+//   E = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag, also 11 products.
 template <typename T, int FMT>
-__device__ __forceinline__ void side_above(su3<T> &acc, const LinkAt<T, FMT> &U, int mu, int nu,
+__device__ __forceinline__ void side_above_full(su3<T> &acc, const LinkAt<T, FMT> &U, int mu, int nu,
                                            int mp1, int mm1, int mp2, int np1, int np2, T c0,
                                            T c1) {
     su3<T> y = mm(mdmd(U(mu, mm1 + np1, 0), U(nu, mm1, 1)), U(mu, mm1, 1));  // D
@@ -317,7 +496,7 @@ __device__ __forceinline__ void side_above(su3<T> &acc, const LinkAt<T, FMT> &U,
 // D' = U_mu(x-mu-nu)^dag U_nu(x-mu-nu) U_mu(x-mu), T' = U_nu(x+mu-2nu)^dag
 // U_mu(x-2nu)^dag U_nu(x-2nu), E' = U_mu(x+mu) U_nu(x+2mu-nu)^dag U_mu(x+mu-nu)^dag.
 template <typename T, int FMT>
-__device__ __forceinline__ void side_below(su3<T> &acc, const LinkAt<T, FMT> &U, int mu, int nu,
+__device__ __forceinline__ void side_below_full(su3<T> &acc, const LinkAt<T, FMT> &U, int mu, int nu,
                                            int mp1, int mm1, int mp2, int nm1, int nm2, T c0,
                                            T c1) {
     su3<T> y = mm(mdm(U(mu, mm1 + nm1, 0), U(nu, mm1 + nm1, 0)), U(mu, mm1, 1));  // D'
@@ -355,11 +534,12 @@ void staple_kernel(StapleArgs a) {
     const uint32_t h = valid ? pencil_site(g, a.tile, j) : 0;
     const int mu = slot >> 1, P = slot & 1;
 
-    su3<T> acc;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) acc.e[i][k] = {T(0), T(0)};
+    // one thread per link: the last factor of the backward paths is taken once for all six
+    // sides; two: a second sum of 9 entries would cost each wave more than it saves
+    constexpr bool kBack = TPL == 1 && FMT != FMT_C128_18;
+    su3<T> acc, back;
+    set_zero(acc);
+    if (kBack) set_zero(back);
 
     if (valid) {
         const Site s = site_coords(g, P, h);
@@ -380,12 +560,26 @@ void staple_kernel(StapleArgs a) {
             const int xn = (int)pick4(s.x[0], s.x[1], s.x[2], s.x[3], nu);
             const int nn = (int)pick4(g.N[0], g.N[1], g.N[2], g.N[3], nu);
             const int sn = (int)pick4(st[0], st[1], st[2], st[3], nu);
-            if (TPL == 1 || q == 0)
-                side_above(acc, U, mu, nu, mp1, mm1, mp2, lex_step(xn, 1, nn, sn),
-                           lex_step(xn, 2, nn, sn), c0, c1);
-            if (TPL == 1 || q == 1)
-                side_below(acc, U, mu, nu, mp1, mm1, mp2, lex_step(xn, -1, nn, sn),
-                           lex_step(xn, -2, nn, sn), c0, c1);
+            const int np1 = lex_step(xn, 1, nn, sn), np2 = lex_step(xn, 2, nn, sn);
+            const int nm1 = lex_step(xn, -1, nn, sn), nm2 = lex_step(xn, -2, nn, sn);
+            if (TPL == 1 || q == 0) {
+                if constexpr (FMT == FMT_C128_18)
+                    side_above_full(acc, U, mu, nu, mp1, mm1, mp2, np1, np2, c0, c1);
+                else
+                    side_above<T, FMT, kBack>(acc, back, U, mu, nu, mp1, mm1, mp2, np1, np2, c0,
+                                              c1);
+            }
+            if (TPL == 1 || q == 1) {
+                if constexpr (FMT == FMT_C128_18)
+                    side_below_full(acc, U, mu, nu, mp1, mm1, mp2, nm1, nm2, c0, c1);
+                else
+                    side_below<T, FMT, kBack>(acc, back, U, mu, nu, mp1, mm1, mp2, nm1, nm2, c0,
+                                              c1);
+            }
+        }
+        if constexpr (kBack) {
+            scale(back, c1);
+            mm_acc(acc, back, U(mu, mm1, 1));
         }
     }
     if (TPL == 2) {
@@ -906,8 +1100,11 @@ __global__ __launch_bounds__(2 * kStapleLinks) void stout_back2_kernel(StoutBack
         }
 }
 
+// FP64-18 links: at most two waves per SIMD.  At three (136 registers) the neighbourhoods
+// of the links in flight outgrow the L2 of the XCD: 857 us against 677 at 32^4.
 template <int FMT>
-__global__ __launch_bounds__(kStoutBlock) void stout_kernel(StoutArgs a) {
+__global__ __launch_bounds__(kStoutBlock)
+__attribute__((amdgpu_waves_per_eu(1, FMT == FMT_C128_18 ? 2 : 8))) void stout_kernel(StoutArgs a) {
     const Geom &g = a.geom;
     const uint32_t blk = a.xcd_remap ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
     const int slot = (int)(blk % 8);

@@ -28,9 +28,18 @@ inline uint32_t staple_blocks(uint32_t Vh) {
     return 8u * ((Vh + kStapleLinks - 1) / kStapleLinks);
 }
 
-// Threads per link the format gets by default: 2 (the two sides of the link on
-// separate waves) for FP64 links, 1 for FP32 ones.
-inline int staple_default_threads(int fmt) { return (fmt == FMT_C128_18 || fmt == FMT_C128_12) ? 2 : 1; }
+// Threads per link by default.  2 (the two sides of the link on separate waves) for
+// FP64-18 links, whose one-thread kernel needs more than 256 registers and runs one wave
+// per SIMD, and for the other formats on small lattices, where one wave per 64 links does
+// not fill the chip (one / two threads, us: 12 x 8 x 10 x 6, Vh 2880, FP64-12 25.3 / 20.5,
+// FP32-12 18.6 / 15.1, BF16-12 21.2 / 15.6; 12^4, Vh 10368, 44.7 / 45.4, 24.3 / 23.3,
+// 25.8 / 25.1; 16^3 x 8, Vh 16384, 50.1 / 56.3, 27.4 / 36.0, 29.1 / 39.4; 32^4 momentum
+// update 1763 / 1808, 886 / 1103).
+constexpr uint32_t kStapleSplitVh = 8192;
+
+inline int staple_default_threads(int fmt, uint32_t Vh) {
+    return (fmt == FMT_C128_18 || Vh < kStapleSplitVh) ? 2 : 1;
+}
 
 // 0: launched; -1: unknown format or thread count (nothing launched).
 int launch_staples(const StapleArgs &a, int fmt, int threads, hipStream_t stream);
