@@ -561,8 +561,9 @@ int stg_batch_workspace_bytes(int nsolve, const stg_solve_desc *descs, int mode,
 
 /*
  * Solves every system of every descriptor.  params->poll_every is the number of
- * iterations per graph replay (0: 16).  stats (host) receives one entry per
- * system, descriptors in order and RHS in order within each.  Returns STG_OK when
+ * iterations per graph replay (0: 8 for small batches, whose replays end with the
+ * true-residual update of the parked systems, else 16).  stats (host) receives one entry
+ * per system, descriptors in order and RHS in order within each.  Returns STG_OK when
  * every system converged, else the worst status.
  */
 int cg_solve_batch(int nsolve, const stg_solve_desc *descs, const stg_cg_params *params, void *ws,

@@ -97,6 +97,19 @@ struct BClass {
     int nr, tps;
     int std_lo, std_hi;  // 1: the class's solves have standard phases (no phase array)
 };
+
+// Classes with 4 threads per site and standard phases that run in one hop launch: the
+// block range [start[c], start[c + 1]) takes the 4 * ntiles[c] tile passes of class c
+// (starts are multiples of the XCD count, so block b still runs on XCD b % 8; the blocks
+// that pad a range exit).
+constexpr int kMergeMax = 4;
+constexpr uint32_t kMergeBlocks = 4096;  // most blocks of a merged launch
+struct BMerge {
+    int n;
+    uint32_t start[kMergeMax + 1];
+    uint32_t tile0[kMergeMax], ntiles[kMergeMax];
+    int nr[kMergeMax];
+};
 int launch_bhop(const BArgs &a, const BClass *cls, int ncls, int fmt, int epi, hipStream_t s);
 int launch_bfinalize(const BArgs &a, int op, hipStream_t s);
 int launch_bcg_update(const BArgs &a, int fp64, hipStream_t s);

@@ -1443,15 +1443,28 @@ int enqueue_batch_update(const BatchPlan &B, int f64, int fmt_hi, hipStream_t s)
 
 thread_local hipStream_t g_capture_stream = nullptr;
 
-// K inner iterations of the whole batch, captured into one executable graph.
-int capture_batch(const BatchPlan &B, int f64, int fmt_in, int K, hipGraph_t &graph,
+// Small batches (all tiles' hop passes in one merged launch, batch.hpp) end every replay
+// with the true-residual update of the systems parked by then.  Its kernels leave the
+// tiles without a parked system alone, so a replay that parks none pays for five launches,
+// and a parked system waits for the end of its replay; with the update launched by the
+// host it waits for the next replay too, and the update drains the stream (16 solves of
+// 8^4 to 16^4: 816 iterations of the batch instead of about 660).  Large batches keep the
+// host's update: there the five launches over every tile cost 1 % (1.250 s against 1.238
+// for 12 solves up to 32^4) and the wait is hidden by the other solves.
+bool batch_inline_update(const BatchPlan &B) { return 4 * B.tiles.size() <= kMergeBlocks; }
+
+// K inner iterations of the whole batch (and the update), captured into one executable
+// graph.
+int capture_batch(const BatchPlan &B, int f64, int fmt_in, int fmt_hi, int K, hipGraph_t &graph,
                   hipGraphExec_t &exec) {
     graph = nullptr;
     exec = nullptr;
     if (!g_capture_stream) HIP_TRY(hipStreamCreateWithFlags(&g_capture_stream, hipStreamNonBlocking));
     HIP_TRY(hipStreamBeginCapture(g_capture_stream, hipStreamCaptureModeThreadLocal));
-    for (int i = 0; i < K; ++i) {
-        const int rc = enqueue_batch_iteration(B, f64, fmt_in, g_capture_stream);
+    const int parts = K + (batch_inline_update(B) ? 1 : 0);
+    for (int i = 0; i < parts; ++i) {
+        const int rc = i < K ? enqueue_batch_iteration(B, f64, fmt_in, g_capture_stream)
+                             : enqueue_batch_update(B, f64, fmt_hi, g_capture_stream);
         if (rc) {
             hipGraph_t junk = nullptr;
             (void)hipStreamEndCapture(g_capture_stream, &junk);
@@ -1470,6 +1483,9 @@ int capture_batch(const BatchPlan &B, int f64, int fmt_in, int K, hipGraph_t &gr
     return STG_OK;
 }
 
+// Iterations per replay of the batch's graph when the caller leaves them open.
+int batch_replay(const BatchPlan &B) { return batch_inline_update(B) ? 8 : 16; }
+
 int run_cg_batch(int nsolve, const stg_solve_desc *d, const stg_cg_params &prm, void *ws,
                  stg_cg_stats *stats, hipStream_t s) {
     const auto t0 = std::chrono::steady_clock::now();
@@ -1481,7 +1497,8 @@ int run_cg_batch(int nsolve, const stg_solve_desc *d, const stg_cg_params &prm, 
     // the classic form unless the single-reduction one is asked for: on the 12-lattice
     // benchmark (same box, same sources) the batch took 1.233 s in the classic form and
     // 1.264 s in the single-reduction one, whose extra step per reliable update and
-    // per solve outweighed the finalize launch it saves
+    // per solve outweighed the finalize launch it saves (small batches gain: 16 solves of
+    // 8^4 to 16^4 take 26.6 ms with it against 29.4)
     B.cgcg = g_cg_form == 2;
     const int fmt_hi = d[0].hi.fmt;
     const int fmt_in = f64 ? fmt_hi : d[0].lo.fmt;
@@ -1545,10 +1562,11 @@ int run_cg_batch(int nsolve, const stg_solve_desc *d, const stg_cg_params &prm, 
 
     // K inner iterations of the whole batch, captured and replayed; captured again
     // over the remaining tiles when finished solves leave enough of them idle
-    int K = prm.poll_every > 0 ? prm.poll_every : 16;
+    int K = prm.poll_every > 0 ? prm.poll_every : batch_replay(B);
+    bool inline_update = batch_inline_update(B);
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    rc = capture_batch(B, f64, fmt_in, K, graph, exec);
+    rc = capture_batch(B, f64, fmt_in, fmt_hi, K, graph, exec);
     if (rc) return rc;
     int replays = 0;
     rc = snapshots_ready(n);
@@ -1561,7 +1579,7 @@ int run_cg_batch(int nsolve, const stg_solve_desc *d, const stg_cg_params &prm, 
             if (st[k].flags & SYS_RUNNING) ++running;
             if (st[k].flags & SYS_RU_PENDING) ++pending;
         }
-        if (pending) {
+        if (pending && !inline_update) {
             if (pend >= 0) {
                 rc = snapshot_wait(n, pend, st);
                 if (rc) break;
@@ -1571,7 +1589,7 @@ int run_cg_batch(int nsolve, const stg_solve_desc *d, const stg_cg_params &prm, 
             if (!rc) rc = read_states_n(B.state, n, st, s);
             continue;
         }
-        if (running == 0) break;
+        if (running + pending == 0) break;
         if (guard.stalled(st)) {
             rc = stall_error();
             break;
@@ -1587,6 +1605,7 @@ int run_cg_batch(int nsolve, const stg_solve_desc *d, const stg_cg_params &prm, 
                 rc = snapshot_wait(n, pend, st);
                 if (rc) break;
                 pend = -1;
+                if (!prune_pays(B, st)) continue;  // nothing left to run
             }
             arrange_tiles(B, &st);
             e = hipMemcpyAsync(B.d_tiles, B.tiles.data(), sizeof(BTile) * B.tiles.size(),
@@ -1597,7 +1616,9 @@ int run_cg_batch(int nsolve, const stg_solve_desc *d, const stg_cg_params &prm, 
             }
             (void)hipGraphExecDestroy(exec);
             (void)hipGraphDestroy(graph);
-            rc = capture_batch(B, f64, fmt_in, K, graph, exec);
+            if (prm.poll_every <= 0) K = batch_replay(B);
+            inline_update = batch_inline_update(B);
+            rc = capture_batch(B, f64, fmt_in, fmt_hi, K, graph, exec);
             if (rc) break;
         }
         hipError_t le = hipGraphLaunch(exec, s);
