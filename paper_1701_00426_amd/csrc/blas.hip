@@ -174,33 +174,45 @@ int launch_p_update_fused(const VecArgs &a, int fp64, hipStream_t stream) {
 // ---------------------------------------------------------------------------
 // single-reduction CG (Chronopoulos and Gear; solver_state.hpp cgcg_step)
 // ---------------------------------------------------------------------------
-// One site's update of one system: p = r + beta p; s = w + beta s; x += alpha p;
-// r -= alpha s; returns the site's |r_new|^2 in FP64.
+// One site's vectors of one system, and their update: p = r + beta p; s = w + beta s;
+// x += alpha p; r -= alpha s; returns the site's |r_new|^2 in FP64.
 template <typename T>
-__device__ __forceinline__ double cgcg_site(const VecArgs &a, size_t o, uint32_t h, T al, T be) {
-    double rr = 0.0;
+struct CgcgSite {
+    vec3<T> r, w, p, sv, x;
+    __device__ __forceinline__ void load(const VecArgs &a, size_t o, uint32_t h) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const size_t i = o + (size_t)c * a.Vh + h;
-        cpx<T> r = ld_c<T>(a.r, i), w = ld_c<T>(a.w, i), p = ld_c<T>(a.p, i),
-               sv = ld_c<T>(a.s, i), x = ld_c<T>(a.x, i);
-        p.re = r.re + be * p.re;
-        p.im = r.im + be * p.im;
-        sv.re = w.re + be * sv.re;
-        sv.im = w.im + be * sv.im;
-        x.re += al * p.re;
-        x.im += al * p.im;
-        r.re -= al * sv.re;
-        r.im -= al * sv.im;
-        st_c<T>(a.p, i, p);
-        st_c<T>(a.s, i, sv);
-        st_c<T>(a.x, i, x);
-        st_c<T>(a.r, i, r);
-        rr = fmat((double)r.re, (double)r.re, rr);
-        rr = fmat((double)r.im, (double)r.im, rr);
+        for (int c = 0; c < 3; ++c) {
+            const size_t i = o + (size_t)c * a.Vh + h;
+            r.c[c] = ld_c<T>(a.r, i);
+            w.c[c] = ld_c<T>(a.w, i);
+            p.c[c] = ld_c<T>(a.p, i);
+            sv.c[c] = ld_c<T>(a.s, i);
+            x.c[c] = ld_c<T>(a.x, i);
+        }
     }
-    return rr;
-}
+    __device__ __forceinline__ double update(const VecArgs &a, size_t o, uint32_t h, T al, T be) {
+        double rr = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const size_t i = o + (size_t)c * a.Vh + h;
+            p.c[c].re = r.c[c].re + be * p.c[c].re;
+            p.c[c].im = r.c[c].im + be * p.c[c].im;
+            sv.c[c].re = w.c[c].re + be * sv.c[c].re;
+            sv.c[c].im = w.c[c].im + be * sv.c[c].im;
+            x.c[c].re += al * p.c[c].re;
+            x.c[c].im += al * p.c[c].im;
+            r.c[c].re -= al * sv.c[c].re;
+            r.c[c].im -= al * sv.c[c].im;
+            st_c<T>(a.p, i, p.c[c]);
+            st_c<T>(a.s, i, sv.c[c]);
+            st_c<T>(a.x, i, x.c[c]);
+            st_c<T>(a.r, i, r.c[c]);
+            rr = fmat((double)r.c[c].re, (double)r.c[c].re, rr);
+            rr = fmat((double)r.c[c].im, (double)r.c[c].im, rr);
+        }
+        return rr;
+    }
+};
 
 template <typename T, int NR>
 __global__ __launch_bounds__(kBlock) void cgcg_update_kernel(VecArgs a) {
@@ -213,37 +225,60 @@ __global__ __launch_bounds__(kBlock) void cgcg_update_kernel(VecArgs a) {
         pc[j] = 0.0;
         const SysState &st = a.state[j];
         if (!(st.flags & SYS_RUNNING) || h >= a.Vh) continue;
-        pair_add(ps[j], pc[j], cgcg_site<T>(a, (size_t)j * a.fstride, h, (T)st.alpha, (T)st.beta),
-                 0.0);
+        CgcgSite<T> v;
+        v.load(a, (size_t)j * a.fstride, h);
+        pair_add(ps[j], pc[j],
+                 v.update(a, (size_t)j * a.fstride, h, (T)st.alpha, (T)st.beta), 0.0);
     }
     block_partials<NR>(ps, pc, a.partials);
 }
 
-// One field, no finalize kernel: every block sums the hop's <r, w> partials and the
+// Compensated sum of n (sum, error) pairs by one wave in a fixed order, in every lane:
+// lane l takes pairs l, l + 64, ..., then a tree across the lanes.
+__device__ __forceinline__ double wave_total(const double *x, uint32_t n) {
+    double s = 0.0, c = 0.0;
+    for (uint32_t i = threadIdx.x & 63; i < n; i += 64) pair_add(s, c, x[2 * i], x[2 * i + 1]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double s2 = __shfl_down(s, off, 64);
+        const double c2 = __shfl_down(c, off, 64);
+        pair_add(s, c, s2, c2);
+    }
+    return __shfl(s + c, 0, 64);
+}
+
+// One field, no finalize kernel: every wave sums the hop's <r, w> partials and the
 // previous update's |r|^2 partials in the same fixed order (bitwise the same totals),
 // takes the scalar step on a copy of the state, and updates its sites; block 0 stores
 // the new state in a.state_out (the next iteration's buffer, never a.state, which the
 // other blocks are reading).  Block 0 always runs, so that a.state_out stays current.
 // A breakdown or a system that parks leaves the vectors alone.
+//
+// On a small lattice the kernel is a chain of latencies, so the waves do without the
+// block's barriers up to the last reduction (a wave sums the few hundred pairs itself;
+// the state of this launch is not written by it, so its flags gate without one), and the
+// site's vectors are loaded before the sums are waited for: 17.1 -> 16.4 us per
+// iteration of 8^4 in FP64.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void cgcg_update_fused_kernel(VecArgs a) {
-    const bool closed = block_gate_closed(a.ctl, a.gate_mask);
-    if (closed && blockIdx.x != 0) return;
     SysState ns = a.state[0];
-    bool left = false, step = false;
+    const bool closed = !(ns.flags & SYS_RUNNING);
+    if (closed && blockIdx.x != 0) return;
+    bool left = false;
     double ps[1] = {0.0}, pc[1] = {0.0};
-    if (!closed && (ns.flags & SYS_RUNNING)) {
-        const double delta = block_total(a.fin_partials, a.fin_blocks);
+    if (!closed) {
+        const uint32_t h = blockIdx.x * kBlock + threadIdx.x;
+        CgcgSite<T> v;
+        if (h < a.Vh) v.load(a, 0, h);
+        const double delta = wave_total(a.fin_partials, a.fin_blocks);
         // just resumed: gamma comes from the state, the partials are stale
         const double gamma = (ns.flags & SYS_RESUME) ? 0.0
-                                                     : block_total(a.fin_partials2, a.fin_blocks2);
+                                                     : wave_total(a.fin_partials2, a.fin_blocks2);
         left = cgcg_step(ns, delta, gamma);
-        step = !left;
-        const uint32_t h = blockIdx.x * kBlock + threadIdx.x;
-        if (step && h < a.Vh)
-            pair_add(ps[0], pc[0], cgcg_site<T>(a, 0, h, (T)ns.alpha, (T)ns.beta), 0.0);
+        if (!left && h < a.Vh)
+            pair_add(ps[0], pc[0], v.update(a, 0, h, (T)ns.alpha, (T)ns.beta), 0.0);
+        block_partials<1>(ps, pc, a.partials);
     }
-    if (!closed) block_partials<1>(ps, pc, a.partials);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         a.state_out[0] = ns;
         if (left) atomicAdd(&a.ctl->n_running, -1);
@@ -347,16 +382,33 @@ __global__ __launch_bounds__(kBlock) void ms_r_update_kernel(VecArgs a) {
 // One block works on one chunk of kBlock sites of one (shift, RHS) pair; a retired pair
 // costs one scalar test per block.  The shift blocks of a chunk sit next to each other in
 // the XCD-ordered block sequence: they run on the same XCD, where the residuals they all
-// read stay in L2.
+// read stay in L2.  After a full ring one more block per chunk updates the base direction
+// of that iteration, p = r + beta p (a.p), which saves a small lattice the launch.
 template <typename T, int M>
 __global__ __launch_bounds__(kBlock) void ms_shift_update_kernel(VecArgs a) {
-    const uint32_t nk = (uint32_t)a.nshift;
+    const uint32_t nk = (uint32_t)a.nshift + (a.p ? 1u : 0u);
     uint32_t b = xcd_block(blockIdx.x, gridDim.x);
     const uint32_t k = b % nk;
     b /= nk;
     const uint32_t nr = (uint32_t)a.nfields;
     const uint32_t j = b % nr;
     const uint32_t h = (b / nr) * kBlock + threadIdx.x;
+    if (k == (uint32_t)a.nshift) {
+        const SysState &s = a.state[j];
+        if (!(s.flags & SYS_RUNNING) || h >= a.Vh) return;
+        const T be = (T)s.beta;
+        const size_t o = (size_t)j * a.fstride + h;
+        const size_t last = (size_t)(a.nsteps - 1) * a.rstride;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const size_t i = o + (size_t)c * a.Vh;
+            cpx<T> p = ld_c<T>(a.p, i), r = ld_c<T>(a.r, last + i);
+            p.re = r.re + be * p.re;
+            p.im = r.im + be * p.im;
+            st_c<T>(a.p, i, p);
+        }
+        return;
+    }
     const Ctl &ctl = *a.ctl;
     const size_t slot = (size_t)ctl.nshift * ctl.nrhs;  // entries per slot of steps
     const ShiftStep *st = ctl.steps + k * ctl.nrhs + a.state[j].gid;
@@ -434,9 +486,9 @@ int launch_cg_update(const VecArgs &a, int fp64, int nr, hipStream_t stream) {
     return launch_finalize(f, stream);
 }
 
-// grid: one block per (chunk of kBlock sites, field, shift)
+// grid: one block per (chunk of kBlock sites, field, shift or, with a.p, base direction)
 int launch_ms_shift_update(const VecArgs &a, int fp64, int slots, hipStream_t stream) {
-    dim3 grid(site_blocks(a.Vh) * (uint32_t)(a.nshift * a.nfields));
+    dim3 grid(site_blocks(a.Vh) * (uint32_t)((a.nshift + (a.p ? 1 : 0)) * a.nfields));
     switch (slots * 2 + (fp64 ? 1 : 0)) {
         case 3: ms_shift_update_kernel<double, 1><<<grid, kBlock, 0, stream>>>(a); return 0;
         case 2: ms_shift_update_kernel<float, 1><<<grid, kBlock, 0, stream>>>(a); return 0;

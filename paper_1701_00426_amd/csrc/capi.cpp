@@ -659,14 +659,29 @@ int read_states(const CgWork &w, int nsys, std::vector<SysState> &st, hipStream_
     return read_states_n(w.state, nsys, st, s);
 }
 
-// Iterations queued between two looks at the flags.  One field: about 4 million site
-// updates (8 to 64 iterations).  Several: the same work shared by the live systems, at
-// least 4 iterations, since a system parked for its true-residual update waits, in every
-// launch of its chunk, until the host has seen it.
+// Whether every run of iterations ends with the true-residual update, queued without a
+// look at the flags (its kernels leave at once when no system is parked): mixed solves on
+// small lattices, whose systems park every few dozen iterations.  Left to the host, each
+// update waited for up to two runs of iterations that had nothing to do, 7 us each: 311
+// iterations of 4^4 with 11 updates took 14.3 ms with runs of 64 iterations and take 5.4;
+// 16^4 with BF16-12 links 23.5 and 10.1; 8^4 with 4 RHS 28.5 and 11.3.
+// On larger lattices the five idle launches cost more than the wait.
+bool inline_update(const CgProblem &P, int live) {
+    return P.mode == STG_CG_MIXED && (P.group == 0 || P.group == P.nsys) &&
+           (uint64_t)P.g.Vh * (uint64_t)live <= (1u << 17);
+}
+
+// Iterations queued between two looks at the flags.  A look costs a copy of a few bytes
+// (4 us on the stream); a system that has parked or converged waits for one to two runs.
+// Small lattices: 12 with the update in the run, else 8 (mixed) or 16 (FP64, where only
+// the end of a system waits); large ones about 4 million site updates, at least 8, or 4
+// when several systems share the launches that wait.
 int poll_iterations(const CgProblem &P, int live) {
     if (P.prm.poll_every > 0) return P.prm.poll_every;
+    if (inline_update(P, live)) return 12;
     const uint32_t work = (1u << 22) / P.g.Vh / (uint32_t)std::max(live, 1);
-    return (int)std::min<uint32_t>(64, std::max<uint32_t>(live > 1 ? 4 : 8, work));
+    const uint32_t most = P.mode == STG_CG_MIXED ? 8 : 16;
+    return (int)std::min<uint32_t>(most, std::max<uint32_t>(live > 1 ? 4 : 8, work));
 }
 
 int run_cg(const CgProblem &P, CgWork w, stg_cg_stats *stats, hipStream_t s) {
@@ -742,15 +757,19 @@ int run_cg(const CgProblem &P, CgWork w, stg_cg_stats *stats, hipStream_t s) {
     StallGuard guard;
     for (;;) {
         int running = 0, pending = 0, live = 0;
+        for (int j = 0; j < n; ++j) live += system_live(st[j]) ? 1 : 0;
+        const bool with_update = inline_update(P, live);
         for (int j = 0; j < n; ++j) {
+            if (with_update) {
+                running += system_live(st[j]) ? 1 : 0;
+                continue;
+            }
             if ((st[j].flags & SYS_RU_PENDING) && seen <= sent[j]) {
                 ++running;  // its update is on the way
-                ++live;
                 continue;
             }
             if (st[j].flags & SYS_RUNNING) ++running;
             if (st[j].flags & SYS_RU_PENDING) ++pending;
-            live += system_live(st[j]) ? 1 : 0;
         }
         if (pending && !running) {
             if (pend >= 0) {
@@ -786,6 +805,12 @@ int run_cg(const CgProblem &P, CgWork w, stg_cg_stats *stats, hipStream_t s) {
         const int poll = poll_iterations(P, live);
         for (int i = 0; i < poll; ++i) {
             rc = enqueue_inner_iteration(P, w, chunks, s);
+            if (rc) return rc;
+        }
+        if (with_update) {
+            std::vector<SysState> due = st;
+            for (int j = 0; j < n; ++j) due[j].flags = system_live(st[j]) ? SYS_RU_PENDING : 0;
+            rc = enqueue_reliable_update(P, w, due, s);
             if (rc) return rc;
         }
         rc = snapshot_enqueue(w.state, n, slot, s);
@@ -925,9 +950,10 @@ size_t ms_workspace(const Geom &g, int nrhs, int nshift, int mode) {
                     carve_cg(g, nrhs * nshift, mode, nullptr).bytes);
 }
 
-// The deferred steps of the first `steps` slots on every shifted system.
+// The deferred steps of the first `steps` slots on every shifted system, and with `base`
+// the base directions of the last of them.
 int enqueue_ms_shift_update(const Geom &g, int f64, int nrhs, int nshift, const MsWork &w,
-                            int steps, hipStream_t s) {
+                            int steps, bool base, hipStream_t s) {
     VecArgs v;
     std::memset(&v, 0, sizeof(v));
     v.Vh = g.Vh;
@@ -940,6 +966,7 @@ int enqueue_ms_shift_update(const Geom &g, int f64, int nrhs, int nshift, const 
     v.nshift = nshift;
     v.nfields = nrhs;
     v.nsteps = steps;
+    v.p = base ? w.p : nullptr;
     v.state = w.state;
     v.ctl = w.ctl;
     VEC_TRY(launch_ms_shift_update(v, f64, w.slots, s));
@@ -987,12 +1014,12 @@ int enqueue_ms_iteration(const Geom &g, const stg_gauge *gg, int f64, int nrhs, 
         v.partials = w.partials;
         v.gate_mask = SYS_RUNNING;
         VEC_TRY(launch_ms_r_update(v, f64, nr, s));
-        VEC_TRY(launch_p_update(v, f64, nr, s));
+        if (slot + 1 < w.slots) VEC_TRY(launch_p_update(v, f64, nr, s));
         j0 += nr;
     }
     HIP_TRY(hipGetLastError());
     if (slot + 1 < w.slots) return STG_OK;
-    return enqueue_ms_shift_update(g, f64, nrhs, nshift, w, w.slots, s);
+    return enqueue_ms_shift_update(g, f64, nrhs, nshift, w, w.slots, true, s);
 }
 
 int run_mscg(const Geom &g, const stg_gauge *hi, const stg_gauge *lo, double mass, int nshift,
@@ -1086,7 +1113,8 @@ int run_mscg(const Geom &g, const stg_gauge *hi, const stg_gauge *lo, double mas
                                s));
     }
     int poll = prm.poll_every;
-    if (poll <= 0) poll = (int)std::min<uint32_t>(64, std::max<uint32_t>(8, (1u << 22) / g.Vh));
+    // as in poll_iterations: on a small lattice up to two runs are idle after the last step
+    if (poll <= 0) poll = (int)std::min<uint32_t>(16, std::max<uint32_t>(8, (1u << 22) / g.Vh));
     rc = snapshots_ready(nrhs);
     if (rc) return rc;
     rc = read_states_n(w.state, nrhs, st, s);
@@ -1120,7 +1148,7 @@ int run_mscg(const Geom &g, const stg_gauge *hi, const stg_gauge *lo, double mas
         slot ^= 1;
     }
     if (ring > 0) {  // the steps of the iterations since the last full ring
-        rc = enqueue_ms_shift_update(g, f64, nrhs, nshift, w, ring, s);
+        rc = enqueue_ms_shift_update(g, f64, nrhs, nshift, w, ring, false, s);
         if (rc) return rc;
     }
     HIP_TRY(hipStreamSynchronize(s));

@@ -265,7 +265,8 @@ int launch_ru_resume(const VecArgs &a, int fp64, int nr, hipStream_t stream);
 // multi-shift: r = r_in - alpha q; |r|^2 -> OP_MS_BETA
 int launch_ms_r_update(const VecArgs &a, int fp64, int nr, hipStream_t stream);
 // multi-shift: the last a.nsteps iterations' x_k += alpha_k p_k and p_k = zeta_k r +
-// beta_k p_k, from a ring of `slots` (1, 2, 4 or 8) residuals
+// beta_k p_k, from a ring of `slots` (1, 2, 4 or 8) residuals; with a.p also p = r + beta p
+// of the last of them
 int launch_ms_shift_update(const VecArgs &a, int fp64, int slots, hipStream_t stream);
 // dst (complex128) = src (complex64), n complex entries
 int launch_c64_to_c128(size_t n, const void *src, void *dst, hipStream_t stream);
