@@ -43,6 +43,26 @@ namespace stg {
 
 namespace {
 
+// row 2 of an SU(3) matrix from rows 0 and 1: conj(row0 x row1), each part one chain of
+// fused operations (24 instead of 30 of rebuild_row2, whose shorter chains suit the hops,
+// and fewer roundings; staples at 32^4 3 % faster)
+template <typename T>
+__device__ __forceinline__ void finish_row2(su3<T> &u) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const cpx<T> a = u.e[0][(j + 1) % 3], b = u.e[1][(j + 2) % 3];
+        const cpx<T> c = u.e[0][(j + 2) % 3], d = u.e[1][(j + 1) % 3];
+        T re = a.re * b.re, im = -a.re * b.im;
+        re = fmat(-a.im, b.im, re);
+        im = fmat(-a.im, b.re, im);
+        re = fmat(-c.re, d.re, re);
+        im = fmat(c.re, d.im, im);
+        re = fmat(c.im, d.im, re);
+        im = fmat(c.im, d.re, im);
+        u.e[2][j] = {re, im};
+    }
+}
+
 // acc += a * conj(b)
 template <typename T>
 __device__ __forceinline__ void cfma_cb(cpx<T> &acc, cpx<T> a, cpx<T> b) {
@@ -239,7 +259,7 @@ struct cached_link<double, FMT_C128_12> {
                 const double2 v = p[(size_t)(a * 3 + b) * Vh];
                 u.e[a][b] = {v.x, v.y};
             }
-        rebuild_row2(u);
+        finish_row2(u);
         return u;
     }
 };
@@ -257,7 +277,7 @@ struct cached_link<float, FMT_C64_12> {
         u.e[1][0] = {c1.z, c1.w};
         u.e[1][1] = {c2.x, c2.y};
         u.e[1][2] = {c2.z, c2.w};
-        rebuild_row2(u);
+        finish_row2(u);
         return u;
     }
 };
@@ -276,10 +296,91 @@ struct cached_link<float, FMT_BF16_12> {
         u.e[1][0] = {bf16_lo(a.w), bf16_hi(a.w)};
         u.e[1][1] = {bf16_lo(b.x), bf16_hi(b.x)};
         u.e[1][2] = {bf16_lo(b.y), bf16_hi(b.y)};
-        rebuild_row2(u);
+        finish_row2(u);
         return u;
     }
 };
+
+// A 12-real link as it is stored: fetched ahead of its use and decoded (third row rebuilt)
+// where it is used.
+template <typename T, int FMT>
+struct RawLink;
+
+template <>
+struct RawLink<double, FMT_C128_12> {
+    double2 w[6];
+    __device__ __forceinline__ void fetch(const void *L, uint32_t Vh, int s, uint32_t h) {
+        const double2 *p = reinterpret_cast<const double2 *>(L) + (size_t)s * 6 * Vh + h;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) w[k] = p[(size_t)k * Vh];
+    }
+    __device__ __forceinline__ su3<double> link() const {
+        su3<double> u;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) u.e[k / 3][k % 3] = {w[k].x, w[k].y};
+        finish_row2(u);
+        return u;
+    }
+};
+
+template <>
+struct RawLink<float, FMT_C64_12> {
+    float4 w[3];
+    __device__ __forceinline__ void fetch(const void *L, uint32_t Vh, int s, uint32_t h) {
+        const float4 *p = reinterpret_cast<const float4 *>(L) + (size_t)s * 3 * Vh + h;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) w[k] = p[(size_t)k * Vh];
+    }
+    __device__ __forceinline__ su3<float> link() const {
+        su3<float> u;
+        u.e[0][0] = {w[0].x, w[0].y};
+        u.e[0][1] = {w[0].z, w[0].w};
+        u.e[0][2] = {w[1].x, w[1].y};
+        u.e[1][0] = {w[1].z, w[1].w};
+        u.e[1][1] = {w[2].x, w[2].y};
+        u.e[1][2] = {w[2].z, w[2].w};
+        finish_row2(u);
+        return u;
+    }
+};
+
+template <>
+struct RawLink<float, FMT_BF16_12> {
+    uint4 a;
+    uint2 b;
+    __device__ __forceinline__ void fetch(const void *L, uint32_t Vh, int s, uint32_t h) {
+        a = reinterpret_cast<const uint4 *>(L)[(size_t)s * Vh + h];
+        b = reinterpret_cast<const uint2 *>(reinterpret_cast<const uint4 *>(L) +
+                                            (size_t)8 * Vh)[(size_t)s * Vh + h];
+    }
+    __device__ __forceinline__ su3<float> link() const {
+        su3<float> u;
+        u.e[0][0] = {bf16_lo(a.x), bf16_hi(a.x)};
+        u.e[0][1] = {bf16_lo(a.y), bf16_hi(a.y)};
+        u.e[0][2] = {bf16_lo(a.z), bf16_hi(a.z)};
+        u.e[1][0] = {bf16_lo(a.w), bf16_hi(a.w)};
+        u.e[1][1] = {bf16_lo(b.x), bf16_hi(b.x)};
+        u.e[1][2] = {bf16_lo(b.y), bf16_hi(b.y)};
+        finish_row2(u);
+        return u;
+    }
+};
+
+// FP64-18 links have no third row to rebuild.
+template <>
+struct RawLink<double, FMT_C128_18> {
+    su3<double> u;
+    __device__ __forceinline__ void fetch(const void *L, uint32_t Vh, int s, uint32_t h) {
+        u = cached_link<double, FMT_C128_18>::load(L, Vh, s, h);
+    }
+    __device__ __forceinline__ su3<double> link() const { return u; }
+};
+
+// Ends a group of fetches: what follows is not scheduled before it, nor the fetches after.
+// Left to itself the compiler issues each link's loads where their values are needed (of
+// the waits of the FP64 staple kernel 33 in 84 were for the load issued last), and two
+// waves per SIMD do not hide that.
+__device__ __forceinline__ void fetched() { __builtin_amdgcn_sched_barrier(0); }
 
 // The links around one site x: lexicographic index L of x, parity P of x.
 template <typename T, int FMT>
@@ -293,6 +394,10 @@ struct LinkAt {
         const uint32_t h = (uint32_t)(L + dl) >> 1;
         return cached_link<T, FMT>::load(links, Vh, 2 * d + par, h);
     }
+    __device__ __forceinline__ void fetch(RawLink<T, FMT> &r, int d, int dl, int flip) const {
+        const int par = (P + flip) & 1;
+        r.fetch(links, Vh, 2 * d + par, (uint32_t)(L + dl) >> 1);
+    }
 };
 
 // The first R rows of a 3x3 matrix.  A product of SU(3) links is SU(3), so two of its
@@ -300,8 +405,11 @@ struct LinkAt {
 // instead of 108, 24 registers of FP64 instead of 36) and completed at the end.  R = 3 for
 // BF16-12 links, whose rows are rounded to 8 bits and not orthonormal to FP32 (FP64-18
 // links, any matrices, take side_*_full).  32^4, staples: FP64-12 1917 -> 1590 us, FP32-12
-// 1080 -> 787, BF16-12 884 -> 857; the FP64 kernel before issued 11 000 vector
-// instructions per link and kept the vector units 65 % busy.
+// 1080 -> 787, BF16-12 884 -> 857 (the FP64 kernel before issued 11 000 vector
+// instructions per link and kept the vector units 65 % busy); with the links fetched ahead
+// and the shorter row rebuild 1432, 724 and 770.  The FP32 kernels are then bound by
+// their instructions, the FP64 one (8 100 instructions per link, 1.1 ms at the 61 TFLOP/s
+// that two waves per SIMD reach) by those and the caches' 16-byte accesses together.
 template <typename T, int R>
 struct rows {
     cpx<T> e[R][3];
@@ -398,75 +506,83 @@ __device__ __forceinline__ void set_zero(su3<T> &c) {
         for (int j = 0; j < 3; ++j) c.e[i][j] = {T(0), T(0)};
 }
 
-// The four paths on the +nu side of the link (header): acc += [c0 X + c1 (Y + Z)] C^dag,
-// and the path whose long side runs backward, X U_mu(x-mu+nu)^dag U_nu(x-mu)^dag U_mu(x-mu):
-// with BACK its last factor, common to all sides, is left to the caller and the product
-// before it is added to back, else c1 times the path is added to acc.
-// mp1 .. np2: lexicographic displacements of x +- mu, x + 2mu, x +- nu, x + 2nu (periodic).
-template <typename T, int FMT, bool BACK>
-__device__ __forceinline__ void side_above(su3<T> &acc, su3<T> &back, const LinkAt<T, FMT> &U,
-                                           int mu, int nu, int mp1, int mm1, int mp2, int np1,
-                                           int np2, T c0, T c1) {
+// The four paths on one side of the link (header; UP: the +nu side, else the -nu side, every
+// U_nu step reversed): acc += [c0 X + c1 (Y + Z)] C, and the path whose long side runs
+// backward, W U_mu(x-mu): with BACK its last factor, common to all sides, is left to the
+// caller and W added to back, else c1 times the path is added to acc.  Every link is
+// fetched one product or more before the one that uses it; u0 holds U_mu(x+mu) on entry
+// and is fetched again for the next side.
+// mp1 .. n2: lexicographic displacements of x +- mu, x + 2mu, x +- nu, x +- 2nu (periodic).
+template <typename T, int FMT, bool BACK, bool UP>
+__device__ __forceinline__ void side(su3<T> &acc, su3<T> &back, RawLink<T, FMT> &u0,
+                                     const LinkAt<T, FMT> &U, int mu, int nu, int mp1, int mm1,
+                                     int mp2, int n1, int n2, T c0, T c1) {
     constexpr int R = chain_rows<FMT>();
+    const auto mulu = [](const rows<T, R> &a, const su3<T> &b) {  // a step along +-nu
+        return UP ? rmul(a, b) : rmuld(a, b);
+    };
+    const auto muld = [](const rows<T, R> &a, const su3<T> &b) {  // a step along -+nu
+        return UP ? rmuld(a, b) : rmul(a, b);
+    };
+    RawLink<T, FMT> p, q;
     su3<T> g;
-    set_zero(g);
-    rows<T, R> a;
-    {
-        const su3<T> b = U(mu, np1, 1);
-        // Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag U_mu(x+nu)^dag
-        a = rmul(rows_of<T, R>(U(mu, mp1, 1)), U(nu, mp2, 0));
-        a = rmuld(a, U(mu, mp1 + np1, 0));
-        a = rmuld(a, b);
-        add_rows(g, c1, a);
-        // X = U_nu(x+mu) U_mu(x+nu)^dag
-        a = rows_of<T, R>(U(nu, mp1, 1));
-        rows<T, R> x = rmuld(a, b);
-        add_rows(g, c0, x);
-        x = rmuld(x, U(mu, mm1 + np1, 0));
-        x = rmuld(x, U(nu, mm1, 1));
-        if constexpr (BACK)
-            add_rows(back, T(1), x);
-        else
-            add_rows(acc, c1, rmul(x, U(mu, mm1, 1)));
-    }
+    // Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag U_mu(x+nu)^dag
+    U.fetch(p, nu, UP ? mp2 : mp2 + n1, UP ? 0 : 1);
+    U.fetch(q, mu, mp1 + n1, 0);
+    fetched();
+    rows<T, R> z = rows_of<T, R>(u0.link());
+    z = mulu(z, p.link());
+    U.fetch(p, nu, UP ? mp1 : mp1 + n1, UP ? 1 : 0);
+    fetched();
+    z = rmuld(z, q.link());
     // Y = U_nu(x+mu) U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag
-    a = rmul(a, U(nu, mp1 + np1, 0));
-    a = rmuld(a, U(mu, np2, 0));
-    a = rmuld(a, U(nu, np1, 1));
-    add_rows(g, c1, a);
-    mmd_acc(acc, g, U(nu, 0, 0));
-}
-
-// The same on the -nu side, every U_nu step reversed.
-template <typename T, int FMT, bool BACK>
-__device__ __forceinline__ void side_below(su3<T> &acc, su3<T> &back, const LinkAt<T, FMT> &U,
-                                           int mu, int nu, int mp1, int mm1, int mp2, int nm1,
-                                           int nm2, T c0, T c1) {
-    constexpr int R = chain_rows<FMT>();
-    su3<T> g;
+    U.fetch(q, nu, UP ? mp1 + n1 : mp1 + n2, UP ? 0 : 1);
+    fetched();
+    const rows<T, R> a = UP ? rows_of<T, R>(p.link()) : rows_of_dag<T, R>(p.link());
+    U.fetch(p, mu, n2, 0);
+    fetched();
+    rows<T, R> y = mulu(a, q.link());
+    U.fetch(q, nu, UP ? n1 : n2, UP ? 1 : 0);
+    fetched();
+    y = rmuld(y, p.link());
+    U.fetch(p, mu, n1, 1);
+    fetched();
+    y = muld(y, q.link());
     set_zero(g);
-    rows<T, R> a;
+    add_rows(g, c1, y);
+    rows<T, R> x;
     {
-        const su3<T> b = U(mu, nm1, 1);
-        a = rmuld(rows_of<T, R>(U(mu, mp1, 1)), U(nu, mp2 + nm1, 1));
-        a = rmuld(a, U(mu, mp1 + nm1, 0));
-        a = rmuld(a, b);
-        add_rows(g, c1, a);
-        a = rows_of_dag<T, R>(U(nu, mp1 + nm1, 0));
-        rows<T, R> x = rmuld(a, b);
-        add_rows(g, c0, x);
-        x = rmuld(x, U(mu, mm1 + nm1, 0));
-        x = rmul(x, U(nu, mm1 + nm1, 0));
-        if constexpr (BACK)
-            add_rows(back, T(1), x);
-        else
-            add_rows(acc, c1, rmul(x, U(mu, mm1, 1)));
+        const su3<T> b = p.link();
+        z = rmuld(z, b);
+        add_rows(g, c1, z);
+        U.fetch(q, mu, mm1 + n1, 0);
+        fetched();
+        x = rmuld(a, b);  // X = U_nu(x+mu) U_mu(x+nu)^dag
     }
-    a = rmuld(a, U(nu, mp1 + nm2, 1));
-    a = rmuld(a, U(mu, nm2, 0));
-    a = rmul(a, U(nu, nm2, 0));
-    add_rows(g, c1, a);
-    mm_acc(acc, g, U(nu, nm1, 1));
+    U.fetch(p, nu, UP ? mm1 : mm1 + n1, UP ? 1 : 0);
+    fetched();
+    add_rows(g, c0, x);
+    // W = X U_mu(x-mu+nu)^dag U_nu(x-mu)^dag
+    x = rmuld(x, q.link());
+    if constexpr (!BACK) {
+        U.fetch(q, mu, mm1, 1);
+        fetched();
+        x = muld(x, p.link());
+        U.fetch(p, nu, UP ? 0 : n1, UP ? 0 : 1);
+        fetched();
+        add_rows(acc, c1, rmul(x, q.link()));
+    } else {
+        U.fetch(q, nu, UP ? 0 : n1, UP ? 0 : 1);
+        fetched();
+        add_rows(back, T(1), muld(x, p.link()));
+    }
+    U.fetch(u0, mu, mp1, 1);
+    fetched();
+    const su3<T> c = BACK ? q.link() : p.link();
+    if constexpr (UP)
+        mmd_acc(acc, g, c);
+    else
+        mm_acc(acc, g, c);
 }
 
 // The same sums for FP64-18 links, any matrices: chains of three rows in FP64 hold so many
@@ -513,15 +629,16 @@ __device__ __forceinline__ void side_below_full(su3<T> &acc, const LinkAt<T, FMT
 
 // TPL threads per link (1 or 2): a block is TPL waves over the same kStapleLinks
 // links; with 2, wave 0 sums the +nu sides and wave 1 the -nu sides, and wave 0
-// adds wave 1's sums from LDS.  Two waves per SIMD are asked of the FP64 split
-// kernel (it then fits in 256 registers).
+// adds wave 1's sums from LDS.  Two waves per SIMD (256 registers) are asked of the FP64
+// kernels, but not of the one-thread FP64-18 one, which would spill 248 bytes (2049 ->
+// 3107 us at 32^4).
 // EPI 0 writes Sigma; EPI 1 (FP64 or FP32-12 links) instead adds (eps beta / 3) times the
 // traceless Hermitian part of i U Sigma to the link's momentum: P -> P - eps F with the
 // Symanzik gauge force F = -(beta/3) [i U Sigma]_TH, the staples never leaving the
 // kernel.
 template <typename T, int FMT, int TPL, int EPI>
 __global__ __launch_bounds__(kStapleLinks * TPL)
-__attribute__((amdgpu_waves_per_eu((TPL == 2 && sizeof(T) == 8) ? 2 : 1)))
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && (TPL == 2 || FMT != FMT_C128_18) ? 2 : 1)))
 void staple_kernel(StapleArgs a) {
     __shared__ cpx<T> part[9][kStapleLinks];
     const Geom &g = a.geom;
@@ -554,6 +671,8 @@ void staple_kernel(StapleArgs a) {
         const int mp1 = lex_step(xm, 1, nm, sm), mm1 = lex_step(xm, -1, nm, sm);
         const int mp2 = lex_step(xm, 2, nm, sm);
         const T c0 = (T)a.c0, c1 = (T)a.c1;
+        RawLink<T, FMT> u0;
+        if constexpr (FMT != FMT_C128_18) U.fetch(u0, mu, mp1, 1);
 #pragma unroll 1
         for (int k = 1; k < 4; ++k) {
             const int nu = (mu + k) & 3;
@@ -566,15 +685,15 @@ void staple_kernel(StapleArgs a) {
                 if constexpr (FMT == FMT_C128_18)
                     side_above_full(acc, U, mu, nu, mp1, mm1, mp2, np1, np2, c0, c1);
                 else
-                    side_above<T, FMT, kBack>(acc, back, U, mu, nu, mp1, mm1, mp2, np1, np2, c0,
-                                              c1);
+                    side<T, FMT, kBack, true>(acc, back, u0, U, mu, nu, mp1, mm1, mp2, np1, np2,
+                                              c0, c1);
             }
             if (TPL == 1 || q == 1) {
                 if constexpr (FMT == FMT_C128_18)
                     side_below_full(acc, U, mu, nu, mp1, mm1, mp2, nm1, nm2, c0, c1);
                 else
-                    side_below<T, FMT, kBack>(acc, back, U, mu, nu, mp1, mm1, mp2, nm1, nm2, c0,
-                                              c1);
+                    side<T, FMT, kBack, false>(acc, back, u0, U, mu, nu, mp1, mm1, mp2, nm1, nm2,
+                                               c0, c1);
             }
         }
         if constexpr (kBack) {
@@ -855,21 +974,27 @@ __device__ __forceinline__ herm3 stout_q(const su3<double> &om) {
 // The traceless anti-Hermitian matrix G of a link between the two passes: the imaginary
 // parts of G00 and G11 (G22 = -G00 - G11), then G01, G02, G12: four 16-byte words,
 // [slot][word][site].
-__device__ __forceinline__ su3<double> load_g(const void *ws, uint32_t Vh, int s, uint32_t h) {
-    const double2 *p = reinterpret_cast<const double2 *>(ws) + (size_t)s * 4 * Vh + h;
-    const double2 d = p[0], a = p[Vh], b = p[2 * (size_t)Vh], c = p[3 * (size_t)Vh];
-    su3<double> g;
-    g.e[0][0] = {0.0, d.x};
-    g.e[1][1] = {0.0, d.y};
-    g.e[2][2] = {0.0, -d.x - d.y};
-    g.e[0][1] = {a.x, a.y};
-    g.e[0][2] = {b.x, b.y};
-    g.e[1][2] = {c.x, c.y};
-    g.e[1][0] = {-a.x, a.y};
-    g.e[2][0] = {-b.x, b.y};
-    g.e[2][1] = {-c.x, c.y};
-    return g;
-}
+struct RawG {
+    double2 w[4];
+    __device__ __forceinline__ void fetch(const void *ws, uint32_t Vh, int s, uint32_t h) {
+        const double2 *p = reinterpret_cast<const double2 *>(ws) + (size_t)s * 4 * Vh + h;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[k] = p[(size_t)k * Vh];
+    }
+    __device__ __forceinline__ su3<double> mat() const {
+        su3<double> g;
+        g.e[0][0] = {0.0, w[0].x};
+        g.e[1][1] = {0.0, w[0].y};
+        g.e[2][2] = {0.0, -w[0].x - w[0].y};
+        g.e[0][1] = {w[1].x, w[1].y};
+        g.e[0][2] = {w[2].x, w[2].y};
+        g.e[1][2] = {w[3].x, w[3].y};
+        g.e[1][0] = {-w[1].x, w[1].y};
+        g.e[2][0] = {-w[2].x, w[2].y};
+        g.e[2][1] = {-w[3].x, w[3].y};
+        return g;
+    }
+};
 
 __device__ __forceinline__ cpx<double> trace_mul(const su3<double> &a, const su3<double> &b) {
     cpx<double> t = {0.0, 0.0};
@@ -1013,7 +1138,9 @@ __global__ __launch_bounds__(kStoutBlock) void stout_back1_kernel(StoutBackArgs 
 //   V1^dag [ V2^dag (H1 - H3) + H5 V2^dag ] V3:
 // 10 matrix products and 60 16-byte loads of the 12-real links and the G per direction
 // (12 and 126 when the six products were taken one by one from stored U^dag G), which is
-// what bounds the pass (1128 -> 869 us at 24^3 x 48).
+// what bounds the pass: both passes together 2107 -> 1213 us at 24^3
+// x 48, and 1114 with every matrix fetched a product ahead, at two waves per SIMD (three, in
+// 168 registers, spill: 1193).
 template <int FMT>
 __global__ __launch_bounds__(2 * kStapleLinks) void stout_back2_kernel(StoutBackArgs a) {
     // two waves over the same kStapleLinks links: wave 0 sums the +b sides, wave 1 the -b
@@ -1040,8 +1167,8 @@ __global__ __launch_bounds__(2 * kStapleLinks) void stout_back2_kernel(StoutBack
         const int L = (int)s.x[0] + st[1] * (int)s.x[1] + st[2] * (int)s.x[2] +
                       st[3] * (int)s.x[3];
         const LinkAt<double, FMT> U{a.links, g.Vh, L, P};
-        const auto G = [&](int d, int dl, int flip) {
-            return load_g(a.ws, g.Vh, 2 * d + ((P + flip) & 1), (uint32_t)(L + dl) >> 1);
+        const auto fetch_g = [&](RawG &r, int d, int dl, int flip) {
+            r.fetch(a.ws, g.Vh, 2 * d + ((P + flip) & 1), (uint32_t)(L + dl) >> 1);
         };
         const int xv = (int)pick4(s.x[0], s.x[1], s.x[2], s.x[3], nu);
         const int nv = (int)pick4(g.N[0], g.N[1], g.N[2], g.N[3], nu);
@@ -1053,28 +1180,50 @@ __global__ __launch_bounds__(2 * kStapleLinks) void stout_back2_kernel(StoutBack
             const int xb = (int)pick4(s.x[0], s.x[1], s.x[2], s.x[3], b);
             const int nb = (int)pick4(g.N[0], g.N[1], g.N[2], g.N[3], b);
             const int sb = (int)pick4(st[0], st[1], st[2], st[3], b);
+            RawLink<double, FMT> u, v;
+            RawG m, n;
             if (q == 0) {
                 const int bp1 = lex_step(xb, 1, nb, sb);
-                const su3<double> p = mmd(U(b, vp1, 1), U(nu, bp1, 1));
-                su3<double> t = mm(p, G(nu, bp1, 1));
-                mm_sub(t, G(b, vp1, 1), p);
-                const su3<double> u3 = U(b, 0, 0);
+                U.fetch(u, b, vp1, 1);
+                U.fetch(v, nu, bp1, 1);
+                fetch_g(m, nu, bp1, 1);
+                fetched();
+                const su3<double> p = mmd(u.link(), v.link());
+                fetch_g(n, b, vp1, 1);
+                fetched();
+                su3<double> t = mm(p, m.mat());
+                U.fetch(u, b, 0, 0);
+                fetched();
+                mm_sub(t, n.mat(), p);
+                fetch_g(m, b, 0, 0);
+                fetched();
+                const su3<double> u3 = u.link();
                 mmd_acc(acc, t, u3);
-                mm_acc(acc, mmd(p, u3), G(b, 0, 0));
+                mm_acc(acc, mmd(p, u3), m.mat());
             } else {
                 const int bm1 = lex_step(xb, -1, nb, sb);
-                const su3<double> v2 = U(nu, bm1, 1);
-                su3<double> d = G(nu, bm1, 1);
+                U.fetch(v, nu, bm1, 1);
+                fetch_g(m, nu, bm1, 1);
+                fetch_g(n, b, bm1, 1);
+                fetched();
+                su3<double> d = m.mat();
                 {
-                    const su3<double> h3 = G(b, bm1, 1);
+                    const su3<double> h3 = n.mat();
 #pragma unroll
                     for (int i = 0; i < 3; ++i)
 #pragma unroll
                         for (int c = 0; c < 3; ++c) d.e[i][c] = csub(d.e[i][c], h3.e[i][c]);
                 }
+                const su3<double> v2 = v.link();
+                fetch_g(m, b, bm1 + vp1, 0);
+                fetched();
                 su3<double> t = mdm(v2, d);
-                mmd_acc(t, G(b, bm1 + vp1, 0), v2);
-                mm_acc(acc, mdm(U(b, bm1 + vp1, 0), t), U(b, bm1, 1));
+                U.fetch(u, b, bm1 + vp1, 0);
+                fetched();
+                mmd_acc(t, m.mat(), v2);
+                U.fetch(v, b, bm1, 1);
+                fetched();
+                mm_acc(acc, mdm(u.link(), t), v.link());
             }
         }
     }
