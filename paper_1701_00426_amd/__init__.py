@@ -18,6 +18,7 @@ phases float64 (8, Vh) or None for the standard staggered phases, fields
 from __future__ import annotations
 
 import ctypes
+import functools
 from dataclasses import dataclass
 from typing import Optional
 
@@ -51,9 +52,20 @@ def library():
     return _lib.load()
 
 
+# The marshalling below is kept short: on a small lattice the binding takes longer than
+# the kernel (8^4 D_oe: 9.5 us per call back to back, 3.4 of them the kernel, and
+# now 6.1).
+# Pointers go to ctypes as integers (the argument types convert them), and the extents as
+# a structure that is built once per lattice and only read by the library.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t: Optional[torch.Tensor]):
@@ -63,7 +75,17 @@ def _ptr(t: Optional[torch.Tensor]):
         raise ValueError("tensor must be on the GPU")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+@functools.lru_cache(maxsize=256)
+def _lattice_of(dims: tuple):
+    """(pointer argument, half volume) of the extents."""
+    return ctypes.byref(_lib.lattice(dims)), half_volume(dims)
+
+
+def _lat(dims):
+    return _lattice_of(tuple(dims))[0]
 
 
 def _field_type(t: torch.Tensor) -> int:
@@ -75,13 +97,14 @@ def _field_type(t: torch.Tensor) -> int:
 
 
 def _nrhs(t: torch.Tensor, vh: int) -> int:
-    if t.dim() == 2:
-        if tuple(t.shape) != (3, vh):
-            raise ValueError(f"field shape {tuple(t.shape)} != (3, {vh})")
+    shape = t.shape
+    if len(shape) == 2:
+        if shape[0] != 3 or shape[1] != vh:
+            raise ValueError(f"field shape {tuple(shape)} != (3, {vh})")
         return 1
-    if t.dim() != 3 or tuple(t.shape[1:]) != (3, vh):
-        raise ValueError(f"field shape {tuple(t.shape)} != (nrhs, 3, {vh})")
-    return int(t.shape[0])
+    if len(shape) != 3 or shape[1] != 3 or shape[2] != vh:
+        raise ValueError(f"field shape {tuple(shape)} != (nrhs, 3, {vh})")
+    return int(shape[0])
 
 
 def half_volume(dims) -> int:
@@ -105,11 +128,8 @@ class Gauge:
     phases: Optional[torch.Tensor] = None
 
     def c(self) -> _lib.StgGauge:
-        g = _lib.StgGauge()
-        g.links = self.links.data_ptr()
-        g.fmt = int(self.fmt)
-        g.phases = self.phases.data_ptr() if self.phases is not None else None
-        return g
+        return _lib.StgGauge(self.links.data_ptr(), int(self.fmt),
+                             self.phases.data_ptr() if self.phases is not None else None)
 
     @property
     def field(self) -> int:
@@ -130,7 +150,7 @@ def stg_get_tuning(key: int) -> int:
 def stg_links_bytes(dims, fmt) -> int:
     n = ctypes.c_size_t(0)
     _lib.check("stg_links_bytes", library().stg_links_bytes(
-        ctypes.byref(_lib.lattice(dims)), int(fmt), ctypes.byref(n)))
+        _lat(dims), int(fmt), ctypes.byref(n)))
     return n.value
 
 
@@ -142,7 +162,7 @@ def stg_pack_links(dims, links_c128_18: torch.Tensor, fmt, stream=None) -> torch
         raise ValueError("links must be complex128 (8, 3, 3, Vh)")
     out = torch.empty(stg_links_bytes(dims, fmt), dtype=torch.uint8, device=links_c128_18.device)
     _lib.check("stg_pack_links", library().stg_pack_links(
-        ctypes.byref(_lib.lattice(dims)), _ptr(links_c128_18), int(fmt), _ptr(out),
+        _lat(dims), _ptr(links_c128_18), int(fmt), _ptr(out),
         _stream(stream)))
     return out
 
@@ -154,7 +174,7 @@ def stg_pack_phases(dims, phases_f64: torch.Tensor, field, stream=None) -> torch
     dt = torch.float64 if field == STG_C128 else torch.float32
     out = torch.empty((8, vh), dtype=dt, device=phases_f64.device)
     _lib.check("stg_pack_phases", library().stg_pack_phases(
-        ctypes.byref(_lib.lattice(dims)), _ptr(phases_f64), int(field), _ptr(out),
+        _lat(dims), _ptr(phases_f64), int(field), _ptr(out),
         _stream(stream)))
     return out
 
@@ -175,16 +195,15 @@ def pack_gauge(dims, links_c128_18: torch.Tensor, fmt, phases_f64: Optional[torc
 
 
 def _apply(name, gauge: Gauge, vin: torch.Tensor, out: Optional[torch.Tensor], stream):
-    vh = half_volume(gauge.dims)
+    lat, vh = _lattice_of(tuple(gauge.dims))
     nrhs = _nrhs(vin, vh)
     if out is None:
         out = torch.empty_like(vin)
-    if out.dtype != vin.dtype or out.shape != vin.shape:
+    elif out.dtype != vin.dtype or out.shape != vin.shape:
         raise ValueError("out must match in")
-    g = gauge.c()
     fn = getattr(library(), name)
-    _lib.check(name, fn(ctypes.byref(_lib.lattice(gauge.dims)), ctypes.byref(g), _field_type(vin),
-                        nrhs, _ptr(vin), _ptr(out), _stream(stream)))
+    _lib.check(name, fn(lat, ctypes.byref(gauge.c()), _field_type(vin), nrhs, _ptr(vin),
+                        _ptr(out), _stream(stream)))
     return out
 
 
@@ -204,7 +223,7 @@ def gauge_staples(gauge: Gauge, c0: float = SYMANZIK_C0, c1: float = SYMANZIK_C1
                   out: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """Staples Sigma_mu(x) of every link, (8, 3, 3, Vh): complex128 for the FP64
     link formats, complex64 for the FP32 ones (asynchronous on the stream)."""
-    vh = half_volume(gauge.dims)
+    vh = _lattice_of(tuple(gauge.dims))[1]
     dtype = torch.complex128 if gauge.field == STG_C128 else torch.complex64
     if out is None:
         out = torch.empty((8, 3, 3, vh), dtype=dtype, device=gauge.links.device)
@@ -212,7 +231,7 @@ def gauge_staples(gauge: Gauge, c0: float = SYMANZIK_C0, c1: float = SYMANZIK_C1
         raise ValueError(f"out must be a contiguous {dtype} tensor of shape (8, 3, 3, {vh})")
     g = gauge.c()
     _lib.check("gauge_staples", library().gauge_staples(
-        ctypes.byref(_lib.lattice(gauge.dims)), ctypes.byref(g), float(c0), float(c1), _ptr(out),
+        _lat(gauge.dims), ctypes.byref(g), float(c0), float(c1), _ptr(out),
         _stream(stream)))
     return out
 
@@ -222,7 +241,7 @@ def fermion_force(gauge: Gauge, coeffs, x_even: torch.Tensor, y_odd: Optional[to
     """Derivative G_mu(z) of S = Re phi^dag sum_k a_k X_k with respect to every link,
     from the solutions X_k (complex128, (nshift, 3, Vh)); returns (G (8, 3, 3, Vh),
     Y = D_oe X).  Asynchronous on the stream."""
-    vh = half_volume(gauge.dims)
+    vh = _lattice_of(tuple(gauge.dims))[1]
     coeffs = [float(c) for c in coeffs]
     n = len(coeffs)
     if x_even.dtype != torch.complex128 or tuple(x_even.shape) != (n, 3, vh) or \
@@ -234,7 +253,7 @@ def fermion_force(gauge: Gauge, coeffs, x_even: torch.Tensor, y_odd: Optional[to
     arr = (ctypes.c_double * max(n, 1))(*coeffs)
     g = gauge.c()
     _lib.check("fermion_force", library().fermion_force(
-        ctypes.byref(_lib.lattice(gauge.dims)), ctypes.byref(g), n, arr, _ptr(x_even),
+        _lat(gauge.dims), ctypes.byref(g), n, arr, _ptr(x_even),
         _ptr(y_odd), _ptr(out), _stream(stream)))
     return out, y_odd
 
@@ -243,7 +262,7 @@ def stout_smear(gauge: Gauge, rho: float, out: Optional[torch.Tensor] = None,
                 stream=None) -> torch.Tensor:
     """One stout-smearing step of every link: complex128 (8, 3, 3, Vh), the full
     FP64 link layout (asynchronous on the stream)."""
-    vh = half_volume(gauge.dims)
+    vh = _lattice_of(tuple(gauge.dims))[1]
     if out is None:
         out = torch.empty((8, 3, 3, vh), dtype=torch.complex128, device=gauge.links.device)
     elif out.dtype != torch.complex128 or tuple(out.shape) != (8, 3, 3, vh) or \
@@ -251,13 +270,13 @@ def stout_smear(gauge: Gauge, rho: float, out: Optional[torch.Tensor] = None,
         raise ValueError(f"out must be a contiguous complex128 tensor of shape (8, 3, 3, {vh})")
     g = gauge.c()
     _lib.check("stout_smear", library().stout_smear(
-        ctypes.byref(_lib.lattice(gauge.dims)), ctypes.byref(g), float(rho), _ptr(out),
+        _lat(gauge.dims), ctypes.byref(g), float(rho), _ptr(out),
         _stream(stream)))
     return out
 
 
 def _check_mom(gauge: Gauge, mom: torch.Tensor):
-    vh = half_volume(gauge.dims)
+    vh = _lattice_of(tuple(gauge.dims))[1]
     dt = torch.complex64 if gauge.fmt == STG_LINK_C64_12 else torch.complex128
     if mom.dtype != dt or tuple(mom.shape) != (8, 3, 3, vh) or not mom.is_contiguous():
         raise ValueError(f"mom must be a contiguous {dt} tensor of shape (8, 3, 3, {vh})")
@@ -271,7 +290,7 @@ def gauge_momentum_update(gauge: Gauge, mom: torch.Tensor, beta: float, eps: flo
     _check_mom(gauge, mom)
     g = gauge.c()
     _lib.check("gauge_momentum_update", library().gauge_momentum_update(
-        ctypes.byref(_lib.lattice(gauge.dims)), ctypes.byref(g), float(beta), float(c0),
+        _lat(gauge.dims), ctypes.byref(g), float(beta), float(c0),
         float(c1), float(eps), _ptr(mom), _stream(stream)))
     return mom
 
@@ -280,7 +299,7 @@ def gauge_link_update(gauge: Gauge, mom: torch.Tensor, eps: float, stream=None) 
     """U <- exp(i eps P) U in place on gauge.links (FP64 formats or FP32-12)."""
     _check_mom(gauge, mom)
     _lib.check("gauge_link_update", library().gauge_link_update(
-        ctypes.byref(_lib.lattice(gauge.dims)), int(gauge.fmt), _ptr(gauge.links), float(eps),
+        _lat(gauge.dims), int(gauge.fmt), _ptr(gauge.links), float(eps),
         _ptr(mom), _stream(stream)))
     return gauge
 
@@ -290,7 +309,7 @@ def stout_force_backprop(gauge: Gauge, rho: float, sigma_smeared: torch.Tensor,
                          stream=None) -> torch.Tensor:
     """dS/dU for the thin links from dS/dU' of the links smeared once with weight rho
     (complex128 (8, 3, 3, Vh) each; asynchronous on the stream)."""
-    vh = half_volume(gauge.dims)
+    vh = _lattice_of(tuple(gauge.dims))[1]
     shape = (8, 3, 3, vh)
     if sigma_smeared.dtype != torch.complex128 or tuple(sigma_smeared.shape) != shape or \
             not sigma_smeared.is_contiguous():
@@ -301,7 +320,7 @@ def stout_force_backprop(gauge: Gauge, rho: float, sigma_smeared: torch.Tensor,
         if ws is None else ws
     g = gauge.c()
     _lib.check("stout_force_backprop", library().stout_force_backprop(
-        ctypes.byref(_lib.lattice(gauge.dims)), ctypes.byref(g), float(rho),
+        _lat(gauge.dims), ctypes.byref(g), float(rho),
         _ptr(sigma_smeared), _ptr(out), _ptr(ws), _stream(stream)))
     return out
 
@@ -310,13 +329,13 @@ def stg_apply_normal(gauge: Gauge, mass: float, in_even: torch.Tensor, sigma: fl
                      out_even: Optional[torch.Tensor] = None,
                      tmp_odd: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """out = (mass^2 + sigma) in - D_eo D_oe in."""
-    vh = half_volume(gauge.dims)
+    vh = _lattice_of(tuple(gauge.dims))[1]
     nrhs = _nrhs(in_even, vh)
     out_even = torch.empty_like(in_even) if out_even is None else out_even
     tmp_odd = torch.empty_like(in_even) if tmp_odd is None else tmp_odd
     g = gauge.c()
     _lib.check("stg_apply_normal", library().stg_apply_normal(
-        ctypes.byref(_lib.lattice(gauge.dims)), ctypes.byref(g), _field_type(in_even), nrhs,
+        _lat(gauge.dims), ctypes.byref(g), _field_type(in_even), nrhs,
         float(mass), float(sigma), _ptr(in_even), _ptr(out_even), _ptr(tmp_odd), _stream(stream)))
     return out_even
 
@@ -326,11 +345,11 @@ def stg_apply_normal_noalloc(gauge: Gauge, mass: float, in_even: torch.Tensor,
                              stream=None) -> torch.Tensor:
     """out = (mass^2 + sigma) in - D_eo D_oe in, the odd intermediate in the library's
     fixed device scratch array (no allocation by the call; out_even is the caller's)."""
-    vh = half_volume(gauge.dims)
+    vh = _lattice_of(tuple(gauge.dims))[1]
     nrhs = _nrhs(in_even, vh)
     g = gauge.c()
     _lib.check("stg_apply_normal_noalloc", library().stg_apply_normal_noalloc(
-        ctypes.byref(_lib.lattice(gauge.dims)), ctypes.byref(g), _field_type(in_even), nrhs,
+        _lat(gauge.dims), ctypes.byref(g), _field_type(in_even), nrhs,
         float(mass), float(sigma), _ptr(in_even), _ptr(out_even), _stream(stream)))
     return out_even
 
@@ -352,7 +371,7 @@ def stg_dot(x: torch.Tensor, y: torch.Tensor, stream=None):
 def stg_workspace_bytes(dims, nrhs, nshift=0, mode=STG_CG_F64) -> int:
     n = ctypes.c_size_t(0)
     _lib.check("stg_workspace_bytes", library().stg_workspace_bytes(
-        ctypes.byref(_lib.lattice(dims)), int(nrhs), int(nshift), int(mode), ctypes.byref(n)))
+        _lat(dims), int(nrhs), int(nshift), int(mode), ctypes.byref(n)))
     return n.value
 
 
@@ -375,7 +394,7 @@ def cg_solve(hi: Gauge, mass: float, b: torch.Tensor, x: Optional[torch.Tensor] 
     Mixed precision when ``lo`` is given (mode STG_CG_MIXED) unless ``mode`` is
     passed.  Returns (x, status, list of per-RHS stats dicts).
     """
-    vh = half_volume(hi.dims)
+    vh = _lattice_of(tuple(hi.dims))[1]
     if b.dtype != torch.complex128:
         raise ValueError("b must be complex128")
     nrhs = _nrhs(b, vh)
@@ -390,7 +409,7 @@ def cg_solve(hi: Gauge, mass: float, b: torch.Tensor, x: Optional[torch.Tensor] 
     g_hi = hi.c()
     g_lo = lo.c() if lo is not None else None
     st = library().cg_solve(
-        ctypes.byref(_lib.lattice(hi.dims)), ctypes.byref(g_hi),
+        _lat(hi.dims), ctypes.byref(g_hi),
         ctypes.byref(g_lo) if g_lo is not None else None, float(mass), nrhs, _ptr(b), _ptr(x),
         ctypes.byref(prm), _ptr(ws), ws.numel(), stats, _stream(stream))
     if check_status:
@@ -405,7 +424,7 @@ def multishift_cg_solve(hi: Gauge, mass: float, shifts, b: torch.Tensor,
 
     Returns (x complex128 (nshift, nrhs, 3, Vh), status, stats[nshift][nrhs]).
     """
-    vh = half_volume(hi.dims)
+    vh = _lattice_of(tuple(hi.dims))[1]
     if b.dtype != torch.complex128:
         raise ValueError("b must be complex128")
     nrhs = _nrhs(b, vh)
@@ -422,7 +441,7 @@ def multishift_cg_solve(hi: Gauge, mass: float, shifts, b: torch.Tensor,
     g_hi = hi.c()
     g_lo = lo.c() if lo is not None else None
     st = library().multishift_cg_solve(
-        ctypes.byref(_lib.lattice(hi.dims)), ctypes.byref(g_hi),
+        _lat(hi.dims), ctypes.byref(g_hi),
         ctypes.byref(g_lo) if g_lo is not None else None, float(mass), ns, sh, nrhs, _ptr(b),
         _ptr(x), ctypes.byref(prm), _ptr(ws), ws.numel(), stats, _stream(stream))
     if check_status:
@@ -434,7 +453,7 @@ def multishift_cg_solve(hi: Gauge, mass: float, shifts, b: torch.Tensor,
 def stg_rational_workspace_bytes(dims, nrhs: int, nshift: int, mode: int) -> int:
     n = ctypes.c_size_t(0)
     _lib.check("stg_rational_workspace_bytes", library().stg_rational_workspace_bytes(
-        ctypes.byref(_lib.lattice(dims)), int(nrhs), int(nshift), int(mode), ctypes.byref(n)))
+        _lat(dims), int(nrhs), int(nshift), int(mode), ctypes.byref(n)))
     return n.value
 
 
@@ -445,7 +464,7 @@ def rational_apply(hi: Gauge, mass: float, shifts, coeffs, a0: float, b: torch.T
 
     Returns (y complex128 (nrhs, 3, Vh), status, stats[nshift][nrhs]).
     """
-    vh = half_volume(hi.dims)
+    vh = _lattice_of(tuple(hi.dims))[1]
     if b.dtype != torch.complex128:
         raise ValueError("b must be complex128")
     nrhs = _nrhs(b, vh)
@@ -466,7 +485,7 @@ def rational_apply(hi: Gauge, mass: float, shifts, coeffs, a0: float, b: torch.T
     g_hi = hi.c()
     g_lo = lo.c() if lo is not None else None
     st = library().rational_apply(
-        ctypes.byref(_lib.lattice(hi.dims)), ctypes.byref(g_hi),
+        _lat(hi.dims), ctypes.byref(g_hi),
         ctypes.byref(g_lo) if g_lo is not None else None, float(mass), ns, sh, co, float(a0),
         nrhs, _ptr(b), _ptr(y), ctypes.byref(prm), _ptr(ws), ws.numel(), stats, _stream(stream))
     if check_status:
@@ -492,7 +511,7 @@ def cg_solve_batch(solves, mode=None, ws: Optional[torch.Tensor] = None, stream=
     nsys = 0
     for i, sv in enumerate(solves):
         hi, lo, b = sv["hi"], sv.get("lo"), sv["b"]
-        vh = half_volume(hi.dims)
+        vh = _lattice_of(tuple(hi.dims))[1]
         nrhs = _nrhs(b, vh)
         if b.dtype != torch.complex128:
             raise ValueError("b must be complex128")
@@ -536,14 +555,14 @@ def stg_autotune(gauge: Gauge, nrhs: int = 1, cache_path: Optional[str] = None, 
     """Times the hop launch shapes for this gauge field and nrhs fields per launch and
     keeps the fastest (process-wide; appended to cache_path when given).  Returns the
     choice as a dict."""
-    vh = half_volume(gauge.dims)
+    vh = _lattice_of(tuple(gauge.dims))[1]
     cdt = torch.complex128 if gauge.field == STG_C128 else torch.complex64
     vin = torch.zeros((nrhs, 3, vh), dtype=cdt, device=gauge.links.device)
     out = torch.empty_like(vin)
     g = gauge.c()
     lib = library()
     _lib.check("stg_autotune", lib.stg_autotune(
-        ctypes.byref(_lib.lattice(gauge.dims)), ctypes.byref(g), int(gauge.field), int(nrhs),
+        _lat(gauge.dims), ctypes.byref(g), int(gauge.field), int(nrhs),
         _ptr(vin), _ptr(out), cache_path.encode() if cache_path else None, _stream(stream)))
     nr = 8 if nrhs >= 8 else 4 if nrhs >= 4 else nrhs
     choice = stg_autotune_lookup(gauge.dims, gauge.fmt, nr)
@@ -562,7 +581,7 @@ def stg_autotune_load(cache_path: str) -> int:
 def stg_autotune_fields_lookup(dims, fmt):
     """The stored fields per launch (1, 2, 4 or 8) for (dims, fmt), or None."""
     v = ctypes.c_int(0)
-    st = library().stg_autotune_fields_lookup(ctypes.byref(_lib.lattice(dims)), int(fmt),
+    st = library().stg_autotune_fields_lookup(_lat(dims), int(fmt),
                                               ctypes.byref(v))
     if st == _lib.STG_NOT_CONVERGED:
         return None
@@ -573,7 +592,7 @@ def stg_autotune_fields_lookup(dims, fmt):
 def stg_autotune_lookup(dims, fmt, nr: int = 1):
     """The stored launch shape for (dims, fmt, nr), or None."""
     c = _lib.StgTuneChoice()
-    st = library().stg_autotune_lookup(ctypes.byref(_lib.lattice(dims)), int(fmt), int(nr),
+    st = library().stg_autotune_lookup(_lat(dims), int(fmt), int(nr),
                                        ctypes.byref(c))
     if st == _lib.STG_NOT_CONVERGED:
         return None
