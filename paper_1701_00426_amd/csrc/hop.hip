@@ -153,11 +153,12 @@ int launch_hop(const HopArgs &a, int fmt, int nr, int epi, hipStream_t stream) {
     // per site are left open too) and built
     int fpw = a.fields_per_wave;
     const bool automatic = fpw == 0;
-    if (automatic) fpw = a.threads_per_site ? 0 : default_fields_per_wave(fmt, nr);
+    if (automatic) fpw = a.threads_per_site ? 0 : default_fields_per_wave(fmt, nr, a.geom.Vh);
     if (fpw > 0 && nr >= 2) {
         HopArgs b = a;
         b.fields_per_wave = fpw;
-        if (automatic && b.layer_group == 0) b.layer_group = a.layer_group_auto;
+        if (automatic && b.layer_group == 0 && a.geom.Vh > kFieldSplitSmallVh)
+            b.layer_group = a.layer_group_auto;
         const int rc = launch_hop_fsplit(b, fmt, nr, epi, stream);
         if (rc != -1) return rc;  // launched, or refused for lack of partials
     }

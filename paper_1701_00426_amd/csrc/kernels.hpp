@@ -158,18 +158,31 @@ int launch_hop_split(const HopArgs &a, int fmt, int nr, int epi, hipStream_t str
 int launch_hop_fsplit(const HopArgs &a, int fmt, int nr, int epi, hipStream_t stream);
 
 // Fields per wave of the field-split hop when the caller leaves both it and the
-// threads per site open, from 32^4 timings on MI355X with 8 fields (rotating copies):
-// FP64-12 one field per wave (D_eo 206.6 us, normal operator 441.5 us, against 251.1
-// and 537.9 with 2 threads per site), FP32-12 and BF16-12 two (113.8 / 227.7 against
-// 121.9 / 273.8, and 101.7 / 205.8 against 104.1 / 263.9 with 4 threads per site).
-// Other field counts keep the direction-split hop (0).  Such automatic launches also
-// take the layer order with 4 x3 planes per group unless the caller set an order
-// (HopArgs::layer_group_auto): at 32^4 it cut their reads from 1.7 to 1.2 times the
-// algorithmic bytes (FP64-12 D_eo 206.6 -> 192.7 us; FP32-12 about 1 % faster).
-inline int default_fields_per_wave(int fmt, int nr) {
-    if (nr != 8) return 0;
-    if (fmt == FMT_C128_12) return 1;
-    return (fmt == FMT_C64_12 || fmt == FMT_BF16_12) ? 2 : 0;
+// threads per site open (0: the direction-split hop).  Plain / normal-operator times in
+// us on MI355X, 8 fields:
+//   FP64-12: 2 fields per wave (32^4 158.6 / 391 against 182.7 / 412 with one, 20^4 28.2 /
+//     62.7 and 30.7 / 67.4, 8^4 6.0 / 13.0 and 6.1 / 13.0): a wave decodes the link of a
+//     site once for two mat-vecs;
+//   FP32-12, BF16-12: 2 on large lattices (32^4 90.4 / 196 against 90.5 / 199 with one),
+//     1 up to Vh = 65536, where twice the waves hide more of the latency (16^3 x 32
+//     FP32-12 13.3 / 28.4 against 14.7 / 30.5, 8^4 9.1 against 11.0; 20^4 39.3 and 39.2).
+// 4 fields:
+//   FP64-12: 1 from Vh = 8192 on (24^3 x 48 76.8 / 163 against 85.0 / 179 with 4 threads
+//     per site, 12^4 6.0 / 11.8 and 6.3 / 12.2; 8^4 10.4 and 9.9);
+//   FP32-12, BF16-12: 1 up to Vh = 65536 (16^3 x 32 19.5 against 20.6 and 16.7 against
+//     18.1; 20^4 27.0 and 25.6, 23.9 and 23.4).
+// Automatic launches above Vh = 65536 also take the layer order with 4 x3 planes per group
+// unless the caller set an order (HopArgs::layer_group_auto): below, the fields of the
+// planes in flight fit the L2s in half-index order too (16^3 x 32, 8 FP64 fields 53.8
+// against 55.7 with it; 20^4 65.1 and 62.7, 32^4 426 and 391).
+constexpr uint32_t kFieldSplitSmallVh = 65536;
+
+inline int default_fields_per_wave(int fmt, int nr, uint32_t Vh) {
+    const bool small = Vh <= kFieldSplitSmallVh;
+    if (fmt == FMT_C128_12) return nr == 8 ? 2 : (nr == 4 && Vh >= 8192) ? 1 : 0;
+    if (fmt != FMT_C64_12 && fmt != FMT_BF16_12) return 0;
+    if (nr == 8) return small ? 1 : 2;
+    return (nr == 4 && small) ? 1 : 0;
 }
 
 // Threads per site when the caller leaves the choice open, from hop timings at 32^4
