@@ -42,6 +42,32 @@ __device__ __forceinline__ void put_tile_partial(double *partials, const BSolve 
         for (int k = used; k < kTileSlots; ++k) pj[2 * k] = pj[2 * k + 1] = 0.0;
 }
 
+// The block's NR sums of tile t into slot 0, with one barrier for all of them (as
+// block_partials); scratch: 2 * NR * kWaves doubles.
+template <int NR>
+__device__ __forceinline__ void put_tile_sums(double *partials, const BSolve &S, const BTile &t,
+                                              double (&s)[NR], double (&c)[NR], double *scratch) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int j = 0; j < NR; ++j) wave_sum_pair(s[j], c[j]);
+    if (lane == 0) {
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            scratch[2 * (j * kWaves + wave)] = s[j];
+            scratch[2 * (j * kWaves + wave) + 1] = c[j];
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < NR) {
+        const double *p = scratch + 2 * threadIdx.x * kWaves;
+        double v = p[0], e = p[1];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) pair_add(v, e, p[2 * w], p[2 * w + 1]);
+        put_tile_partial(partials, S, t, t.j0 + (int)threadIdx.x, 0, 1, v, e);
+    }
+    __syncthreads();
+}
+
 // Tile ti of the vector kernels is block ti: these kernels reuse nothing between
 // tiles, and the hardware deals consecutive blocks to the XCDs in turn, so every
 // XCD gets its share of each solve's tiles however few solves still run.  The
@@ -206,11 +232,21 @@ __device__ void bhop_tile_split(const BArgs &a, const BSolve &S, const BTile &t,
         }
     }
     if (EPI != EPI_PLAIN) {
-        __shared__ double sh_red[2 * kWaves];
+        if constexpr (TPS == 4) {
+            if (q != 0) return;  // group 0, one wave, holds every site's terms
 #pragma unroll
-        for (int j = 0; j < NR; ++j) {
-            block_sum_pair(ps[j], pc[j], sh_red);
-            if (threadIdx.x == 0) put_tile_partial(a.partials, S, t, t.j0 + j, sub, TPS, ps[j], pc[j]);
+            for (int j = 0; j < NR; ++j) {
+                wave_sum_pair(ps[j], pc[j]);
+                if (l == 0) put_tile_partial(a.partials, S, t, t.j0 + j, sub, TPS, ps[j], pc[j]);
+            }
+        } else {
+            __shared__ double sh_red[2 * kWaves];
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                block_sum_pair(ps[j], pc[j], sh_red);
+                if (threadIdx.x == 0)
+                    put_tile_partial(a.partials, S, t, t.j0 + j, sub, TPS, ps[j], pc[j]);
+            }
         }
     }
 }
@@ -305,17 +341,13 @@ __device__ void bcg_update_tile(const BArgs &a, const BSolve &S, const BTile &t,
         st_v<T>(S.r, fs, S.g.Vh, js, h, r);
         pair_add(ps[j], pc[j], site, 0.0);
     }
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        block_sum_pair(ps[j], pc[j], sh_red);
-        if (threadIdx.x == 0) put_tile_partial(a.partials, S, t, t.j0 + j, 0, 1, ps[j], pc[j]);
-    }
+    put_tile_sums<NR>(a.partials, S, t, ps, pc, sh_red);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void bcg_update_kernel(BArgs a) {
     if (block_gate_closed(a.ctl, a.gate_running)) return;
-    __shared__ double sh_red[2 * kWaves];
+    __shared__ double sh_red[2 * 4 * kWaves];
     FOR_EACH_TILE(a, ti) {
         const BTile t = a.tiles[ti];
         const BSolve &S = a.solves[t.solve];
@@ -411,17 +443,13 @@ __device__ void bcgcg_update_tile(const BArgs &a, const BSolve &S, const BTile &
         st_v<T>(S.r, fs, S.g.Vh, js, h, r);
         pair_add(ps[j], pc[j], site, 0.0);
     }
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        block_sum_pair(ps[j], pc[j], sh_red);
-        if (threadIdx.x == 0) put_tile_partial(a.partials2, S, t, t.j0 + j, 0, 1, ps[j], pc[j]);
-    }
+    put_tile_sums<NR>(a.partials2, S, t, ps, pc, sh_red);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void bcgcg_update_kernel(BArgs a) {
     if (block_gate_closed(a.ctl, a.gate_running)) return;
-    __shared__ double sh_red[2 * kWaves];
+    __shared__ double sh_red[2 * 4 * kWaves];
     FOR_EACH_TILE(a, ti) {
         const BTile t = a.tiles[ti];
         const BSolve &S = a.solves[t.solve];

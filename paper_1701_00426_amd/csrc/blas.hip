@@ -233,18 +233,22 @@ __global__ __launch_bounds__(kBlock) void cgcg_update_kernel(VecArgs a) {
     block_partials<NR>(ps, pc, a.partials);
 }
 
-// Compensated sum of n (sum, error) pairs by one wave in a fixed order, in every lane:
-// lane l takes pairs l, l + 64, ..., then a tree across the lanes.
-__device__ __forceinline__ double wave_total(const double *x, uint32_t n) {
-    double s = 0.0, c = 0.0;
+// Compensated sums of n (sum, error) pairs at x and of m at y by one wave in a fixed order,
+// in every lane: lane l takes pairs l, l + 64, ..., then a tree across the lanes.
+__device__ __forceinline__ void wave_totals(const double *x, uint32_t n, const double *y,
+                                            uint32_t m, double &sx, double &sy) {
+    double s = 0.0, c = 0.0, u = 0.0, v = 0.0;
     for (uint32_t i = threadIdx.x & 63; i < n; i += 64) pair_add(s, c, x[2 * i], x[2 * i + 1]);
+    for (uint32_t i = threadIdx.x & 63; i < m; i += 64) pair_add(u, v, y[2 * i], y[2 * i + 1]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
-        const double s2 = __shfl_down(s, off, 64);
-        const double c2 = __shfl_down(c, off, 64);
+        const double s2 = __shfl_down(s, off, 64), c2 = __shfl_down(c, off, 64);
+        const double u2 = __shfl_down(u, off, 64), v2 = __shfl_down(v, off, 64);
         pair_add(s, c, s2, c2);
+        pair_add(u, v, u2, v2);
     }
-    return __shfl(s + c, 0, 64);
+    sx = __shfl(s + c, 0, 64);
+    sy = __shfl(u + v, 0, 64);
 }
 
 // One field, no finalize kernel: every wave sums the hop's <r, w> partials and the
@@ -270,10 +274,10 @@ __global__ __launch_bounds__(kBlock) void cgcg_update_fused_kernel(VecArgs a) {
         const uint32_t h = blockIdx.x * kBlock + threadIdx.x;
         CgcgSite<T> v;
         if (h < a.Vh) v.load(a, 0, h);
-        const double delta = wave_total(a.fin_partials, a.fin_blocks);
         // just resumed: gamma comes from the state, the partials are stale
-        const double gamma = (ns.flags & SYS_RESUME) ? 0.0
-                                                     : wave_total(a.fin_partials2, a.fin_blocks2);
+        double delta, gamma;
+        wave_totals(a.fin_partials, a.fin_blocks, a.fin_partials2,
+                    (ns.flags & SYS_RESUME) ? 0 : a.fin_blocks2, delta, gamma);
         left = cgcg_step(ns, delta, gamma);
         if (!left && h < a.Vh)
             pair_add(ps[0], pc[0], v.update(a, 0, h, (T)ns.alpha, (T)ns.beta), 0.0);

@@ -361,16 +361,22 @@ __device__ __forceinline__ void pair_add(double &s, double &c, double s2, double
     c += c2 + e;
 }
 
+// Compensated sum of the wave's per-lane (s, c) pairs in a fixed shuffle order;
+// valid in lane 0.
+__device__ __forceinline__ void wave_sum_pair(double &s, double &c) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double s2 = __shfl_down(s, off, 64);
+        const double c2 = __shfl_down(c, off, 64);
+        pair_add(s, c, s2, c2);
+    }
+}
+
 // Compensated block sum of per-thread (s, c) pairs in a fixed order (wave64
 // shuffle tree, then the four waves in order); the pair is valid in thread 0.
 // scratch: 2 * kWaves doubles of shared memory.
 __device__ __forceinline__ void block_sum_pair(double &s, double &c, double *scratch) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        double s2 = __shfl_down(s, off, 64);
-        double c2 = __shfl_down(c, off, 64);
-        pair_add(s, c, s2, c2);
-    }
+    wave_sum_pair(s, c);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) {
         scratch[2 * wave] = s;

@@ -100,17 +100,6 @@ constexpr size_t fsplit_lds_bytes() {
     return (size_t)8 * LinkWords<T, FMT>::W * kFsSites * 16;
 }
 
-// Compensated sum of the wave's per-lane (s, c) pairs in a fixed shuffle order;
-// valid in lane 0.
-__device__ __forceinline__ void wave_sum_pair(double &s, double &c) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double s2 = __shfl_down(s, off, 64);
-        const double c2 = __shfl_down(c, off, 64);
-        pair_add(s, c, s2, c2);
-    }
-}
-
 template <typename T, int FMT, bool STDPH, int NR, int FPG, int EPI>
 __global__ __launch_bounds__(64 * (NR / FPG)) void hop_fsplit_kernel(HopArgs a) {
     constexpr int G = NR / FPG;

@@ -134,7 +134,21 @@ __global__ __launch_bounds__(kBlock) void hop_split_kernel(HopArgs a) {
         }
     }
     if (EPI == EPI_PLAIN || a.op == OP_NONE) return;
-    block_partials<NR>(ps, pc, a.partials);
+    if constexpr (TPS == 4) {
+        // a field's 64 sites are finished by one wave (the first, or its owner's), which
+        // sums them without the block: at 24^3 x 48 with 4 FP32 fields the normal hop with
+        // its reduction took 62.7 us against 44.8 of the plain hop, now 48.2
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            int owner = 0;
+            if constexpr (SPREAD) owner = spread_owner<NR, TPS>(j);
+            if (q != owner) continue;
+            wave_sum_pair(ps[j], pc[j]);
+            if (l == 0) put_partial<NR>(a.partials, j, ps[j], pc[j]);
+        }
+    } else {
+        block_partials<NR>(ps, pc, a.partials);
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -62,19 +62,37 @@ struct HopArgs {
 // NR sums -> one (sum, error) pair per block in `partials` ([NR][grid][2]).  The
 // sums are finished by finalize_kernel, launched right after on the same stream:
 // the kernel boundary makes the partials of every XCD visible without a
-// device-scope fence in each block (which costs an L2 write-back per block).
+// device-scope fence in each block (which costs an L2 write-back per block).  The NR
+// trees across the lanes run interleaved and one barrier serves them all (two per sum
+// before); each sum keeps the order of block_sum_pair.
+template <int NR>
+__device__ __forceinline__ void put_partial(double *partials, int j, double s, double c) {
+    double *pj = partials + 2 * ((size_t)j * gridDim.x + blockIdx.x);
+    pj[0] = s;
+    pj[1] = c;
+}
+
 template <int NR>
 __device__ __forceinline__ void block_partials(double (&s)[NR], double (&c)[NR],
                                                double *partials) {
-    __shared__ double sh_red[2 * kWaves];
+    __shared__ double sh_red[NR][kWaves][2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        block_sum_pair(s[j], c[j], sh_red);
-        if (threadIdx.x == 0) {
-            double *pj = partials + 2 * ((size_t)j * gridDim.x + blockIdx.x);
-            pj[0] = s[j];
-            pj[1] = c[j];
+    for (int j = 0; j < NR; ++j) wave_sum_pair(s[j], c[j]);
+    if (lane == 0) {
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            sh_red[j][wave][0] = s[j];
+            sh_red[j][wave][1] = c[j];
         }
+    }
+    __syncthreads();
+    if (threadIdx.x < NR) {
+        const int j = threadIdx.x;
+        double t = sh_red[j][0][0], e = sh_red[j][0][1];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) pair_add(t, e, sh_red[j][w][0], sh_red[j][w][1]);
+        put_partial<NR>(partials, j, t, e);
     }
 }
 
