@@ -674,14 +674,19 @@ bool inline_update(const CgProblem &P, int live) {
 // Iterations queued between two looks at the flags.  A look costs a copy of a few bytes
 // (4 us on the stream); a system that has parked or converged waits for one to two runs.
 // Small lattices: 12 with the update in the run, else 8 (mixed) or 16 (FP64, where only
-// the end of a system waits); large ones about 4 million site updates, at least 8, or 4
-// when several systems share the launches that wait.
+// the end of a system waits); a large one about 4 million site updates, at least 8.
+// Several systems share launches that go on with their fields while they wait, so there a
+// run is 2 million site-field updates, at least 2 iterations (16 shifts x 2 RHS at 24^3 x
+// 48: 328 ms with at least 4 and twice the work, 324 so; 16^4, 12 x 3: 52.0 and 49.1).
 int poll_iterations(const CgProblem &P, int live) {
     if (P.prm.poll_every > 0) return P.prm.poll_every;
     if (inline_update(P, live)) return 12;
-    const uint32_t work = (1u << 22) / P.g.Vh / (uint32_t)std::max(live, 1);
     const uint32_t most = P.mode == STG_CG_MIXED ? 8 : 16;
-    return (int)std::min<uint32_t>(most, std::max<uint32_t>(live > 1 ? 4 : 8, work));
+    if (live > 1) {
+        const uint32_t work = (1u << 21) / P.g.Vh / (uint32_t)live;
+        return (int)std::min<uint32_t>(most, std::max<uint32_t>(2, work));
+    }
+    return (int)std::min<uint32_t>(most, std::max<uint32_t>(8, (1u << 22) / P.g.Vh));
 }
 
 int run_cg(const CgProblem &P, CgWork w, stg_cg_stats *stats, hipStream_t s) {
