@@ -42,33 +42,14 @@ __device__ __forceinline__ void put_tile_partial(double *partials, const BSolve 
         for (int k = used; k < kTileSlots; ++k) pj[2 * k] = pj[2 * k + 1] = 0.0;
 }
 
-// The block's NR sums of tile t into slot 0, with one barrier for all of them (as
-// block_partials); scratch: 2 * NR * kWaves doubles.
-template <int NR>
-__device__ __forceinline__ void put_tile_sums(double *partials, const BSolve &S, const BTile &t,
-                                              double (&s)[NR], double (&c)[NR], double *scratch) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < NR; ++j) wave_sum_pair(s[j], c[j]);
-    if (lane == 0) {
-#pragma unroll
-        for (int j = 0; j < NR; ++j) {
-            scratch[2 * (j * kWaves + wave)] = s[j];
-            scratch[2 * (j * kWaves + wave) + 1] = c[j];
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < NR) {
-        const double *p = scratch + 2 * threadIdx.x * kWaves;
-        double v = p[0], e = p[1];
-#pragma unroll
-        for (int w = 1; w < kWaves; ++w) pair_add(v, e, p[2 * w], p[2 * w + 1]);
-        put_tile_partial(partials, S, t, t.j0 + (int)threadIdx.x, 0, 1, v, e);
-    }
-    __syncthreads();
+// The block's sum of system js of tile t into slot 0.
+__device__ __forceinline__ void put_tile_sum(double *partials, const BSolve &S, const BTile &t,
+                                             int js, double s, double c, double *scratch) {
+    block_sum_pair(s, c, scratch);
+    if (threadIdx.x == 0) put_tile_partial(partials, S, t, js, 0, 1, s, c);
 }
 
-// Tile ti of the vector kernels is block ti: these kernels reuse nothing between
+// Field blockIdx.y of tile ti of the vector kernels is block ti: these kernels reuse nothing between
 // tiles, and the hardware deals consecutive blocks to the XCDs in turn, so every
 // XCD gets its share of each solve's tiles however few solves still run.  The
 // launches give every tile a block of its own; the loop only guards a grid smaller
@@ -305,74 +286,67 @@ __global__ __launch_bounds__(kBlock) void bhop_merged_kernel(BArgs a, BMerge m) 
 // vector kernels over tiles
 // ---------------------------------------------------------------------------
 
-// x += alpha p; r -= alpha q; partials of |r|^2  (running systems).  Compiled per
-// field count so that the loads of all fields of a tile are issued together and
-// the block reductions follow them.
-template <typename T, int NR>
-__device__ void bcg_update_tile(const BArgs &a, const BSolve &S, const BTile &t,
-                                double *sh_red) {
-    const size_t fs = (size_t)3 * S.g.Vh;
-    const uint32_t h = t.blk * kBlock + threadIdx.x;
-    double ps[NR], pc[NR];
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        ps[j] = pc[j] = 0.0;
-        const int js = t.j0 + j;
-        const SysState &st = a.state[S.sys0 + js];
-        if (!(st.flags & SYS_RUNNING) || h >= S.g.Vh) continue;
-        const T al = (T)st.alpha;
-        // the site's twelve loads first (the stores may alias them as far as the
-        // compiler knows, so loads issued per colour would wait for the stores)
-        vec3<T> x = ld_v<T>(S.xin, fs, S.g.Vh, js, h);
-        const vec3<T> p = ld_v<T>(S.p, fs, S.g.Vh, js, h);
-        vec3<T> r = ld_v<T>(S.r, fs, S.g.Vh, js, h);
-        const vec3<T> q = ld_v<T>(S.q, fs, S.g.Vh, js, h);
-        double site = 0.0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            x.c[c].re += al * p.c[c].re;
-            x.c[c].im += al * p.c[c].im;
-            r.c[c].re -= al * q.c[c].re;
-            r.c[c].im -= al * q.c[c].im;
-            site = fmat((double)r.c[c].re, (double)r.c[c].re, site);
-            site = fmat((double)r.c[c].im, (double)r.c[c].im, site);
-        }
-        st_v<T>(S.xin, fs, S.g.Vh, js, h, x);
-        st_v<T>(S.r, fs, S.g.Vh, js, h, r);
-        pair_add(ps[j], pc[j], site, 0.0);
-    }
-    put_tile_sums<NR>(a.partials, S, t, ps, pc, sh_red);
+// The field of a tile that a block of the vector kernels works on (blockIdx.y; the grid
+// covers the most fields of any tile): false when the tile has no such field or its
+// system has none of the flags.  A block per field, not all of a tile's fields in one
+// thread: 16 solves of 8^4 to 16^4, x / r update 8.6 -> 5.4 us, p update 5.1 -> 3.8;
+// 12 solves up to 32^4 1.231 -> 1.141 s.
+__device__ __forceinline__ bool tile_field(const BArgs &a, const BSolve &S, const BTile &t,
+                                           int flags, int &js) {
+    js = t.j0 + (int)blockIdx.y;
+    return blockIdx.y < t.nr && (a.state[S.sys0 + js].flags & flags) != 0;
 }
 
+// x += alpha p; r -= alpha q; partials of |r|^2  (running systems)
 template <typename T>
 __global__ __launch_bounds__(kBlock) void bcg_update_kernel(BArgs a) {
-    if (block_gate_closed(a.ctl, a.gate_running)) return;
-    __shared__ double sh_red[2 * 4 * kWaves];
+    __shared__ double sh_red[2 * kWaves];
     FOR_EACH_TILE(a, ti) {
         const BTile t = a.tiles[ti];
         const BSolve &S = a.solves[t.solve];
-        if (!tile_active(a, S, t)) continue;
-        switch (t.nr) {
-            case 1: bcg_update_tile<T, 1>(a, S, t, sh_red); break;
-            case 2: bcg_update_tile<T, 2>(a, S, t, sh_red); break;
-            case 3: bcg_update_tile<T, 3>(a, S, t, sh_red); break;
-            default: bcg_update_tile<T, 4>(a, S, t, sh_red); break;
+        int js;
+        if (!tile_field(a, S, t, SYS_RUNNING, js)) continue;
+        const size_t fs = (size_t)3 * S.g.Vh;
+        const uint32_t h = t.blk * kBlock + threadIdx.x;
+        double ps = 0.0, pc = 0.0;
+        if (h < S.g.Vh) {
+            const T al = (T)a.state[S.sys0 + js].alpha;
+            // the site's twelve loads first (the stores may alias them as far as the
+            // compiler knows, so loads issued per colour would wait for the stores)
+            vec3<T> x = ld_v<T>(S.xin, fs, S.g.Vh, js, h);
+            const vec3<T> p = ld_v<T>(S.p, fs, S.g.Vh, js, h);
+            vec3<T> r = ld_v<T>(S.r, fs, S.g.Vh, js, h);
+            const vec3<T> q = ld_v<T>(S.q, fs, S.g.Vh, js, h);
+            double site = 0.0;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                x.c[c].re += al * p.c[c].re;
+                x.c[c].im += al * p.c[c].im;
+                r.c[c].re -= al * q.c[c].re;
+                r.c[c].im -= al * q.c[c].im;
+                site = fmat((double)r.c[c].re, (double)r.c[c].re, site);
+                site = fmat((double)r.c[c].im, (double)r.c[c].im, site);
+            }
+            st_v<T>(S.xin, fs, S.g.Vh, js, h, x);
+            st_v<T>(S.r, fs, S.g.Vh, js, h, r);
+            pair_add(ps, pc, site, 0.0);
         }
+        put_tile_sum(a.partials, S, t, js, ps, pc, sh_red);
     }
 }
 
 // p = r + beta p  (running systems)
-template <typename T, int NR>
-__device__ __forceinline__ void bp_update_tile(const BArgs &a, const BSolve &S, const BTile &t) {
-    const size_t fs = (size_t)3 * S.g.Vh;
-    const uint32_t h = t.blk * kBlock + threadIdx.x;
-    if (h >= S.g.Vh) return;
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        const int js = t.j0 + j;
-        const SysState &st = a.state[S.sys0 + js];
-        if (!(st.flags & SYS_RUNNING)) continue;
-        const T be = (T)st.beta;
+template <typename T>
+__global__ __launch_bounds__(kBlock) void bp_update_kernel(BArgs a) {
+    FOR_EACH_TILE(a, ti) {
+        const BTile t = a.tiles[ti];
+        const BSolve &S = a.solves[t.solve];
+        int js;
+        if (!tile_field(a, S, t, SYS_RUNNING, js)) continue;
+        const size_t fs = (size_t)3 * S.g.Vh;
+        const uint32_t h = t.blk * kBlock + threadIdx.x;
+        if (h >= S.g.Vh) continue;
+        const T be = (T)a.state[S.sys0 + js].beta;
         vec3<T> p = ld_v<T>(S.p, fs, S.g.Vh, js, h);  // loads first, as above
         const vec3<T> r = ld_v<T>(S.r, fs, S.g.Vh, js, h);
 #pragma unroll
@@ -384,82 +358,51 @@ __device__ __forceinline__ void bp_update_tile(const BArgs &a, const BSolve &S, 
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kBlock) void bp_update_kernel(BArgs a) {
-    if (a.gate_running && a.ctl->n_running == 0) return;
-    FOR_EACH_TILE(a, ti) {
-        const BTile t = a.tiles[ti];
-        const BSolve &S = a.solves[t.solve];
-        if (!tile_active(a, S, t)) continue;
-        switch (t.nr) {
-            case 1: bp_update_tile<T, 1>(a, S, t); break;
-            case 2: bp_update_tile<T, 2>(a, S, t); break;
-            case 3: bp_update_tile<T, 3>(a, S, t); break;
-            default: bp_update_tile<T, 4>(a, S, t); break;
-        }
-    }
-}
-
 // Single-reduction form (Chronopoulos and Gear, solver_state.hpp cgcg_step), running
 // systems: p = r + beta p, s = w + beta s (s = A p by recurrence; w = A r is in q),
 // x += alpha p, r -= alpha s, and the new |r|^2 partials into partials2 for the next
 // step's finalize.
-template <typename T, int NR>
-__device__ void bcgcg_update_tile(const BArgs &a, const BSolve &S, const BTile &t,
-                                  double *sh_red) {
-    const size_t fs = (size_t)3 * S.g.Vh;
-    const uint32_t h = t.blk * kBlock + threadIdx.x;
-    double ps[NR], pc[NR];
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        ps[j] = pc[j] = 0.0;
-        const int js = t.j0 + j;
-        const SysState &st = a.state[S.sys0 + js];
-        if (!(st.flags & SYS_RUNNING) || h >= S.g.Vh) continue;
-        const T al = (T)st.alpha, be = (T)st.beta;
-        // the site's fifteen loads first, as in the x/r update
-        vec3<T> r = ld_v<T>(S.r, fs, S.g.Vh, js, h);
-        const vec3<T> w = ld_v<T>(S.q, fs, S.g.Vh, js, h);
-        vec3<T> p = ld_v<T>(S.p, fs, S.g.Vh, js, h);
-        vec3<T> sv = ld_v<T>(S.s, fs, S.g.Vh, js, h);
-        vec3<T> x = ld_v<T>(S.xin, fs, S.g.Vh, js, h);
-        double site = 0.0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            p.c[c].re = r.c[c].re + be * p.c[c].re;
-            p.c[c].im = r.c[c].im + be * p.c[c].im;
-            sv.c[c].re = w.c[c].re + be * sv.c[c].re;
-            sv.c[c].im = w.c[c].im + be * sv.c[c].im;
-            x.c[c].re += al * p.c[c].re;
-            x.c[c].im += al * p.c[c].im;
-            r.c[c].re -= al * sv.c[c].re;
-            r.c[c].im -= al * sv.c[c].im;
-            site = fmat((double)r.c[c].re, (double)r.c[c].re, site);
-            site = fmat((double)r.c[c].im, (double)r.c[c].im, site);
-        }
-        st_v<T>(S.p, fs, S.g.Vh, js, h, p);
-        st_v<T>(S.s, fs, S.g.Vh, js, h, sv);
-        st_v<T>(S.xin, fs, S.g.Vh, js, h, x);
-        st_v<T>(S.r, fs, S.g.Vh, js, h, r);
-        pair_add(ps[j], pc[j], site, 0.0);
-    }
-    put_tile_sums<NR>(a.partials2, S, t, ps, pc, sh_red);
-}
-
 template <typename T>
 __global__ __launch_bounds__(kBlock) void bcgcg_update_kernel(BArgs a) {
-    if (block_gate_closed(a.ctl, a.gate_running)) return;
-    __shared__ double sh_red[2 * 4 * kWaves];
+    __shared__ double sh_red[2 * kWaves];
     FOR_EACH_TILE(a, ti) {
         const BTile t = a.tiles[ti];
         const BSolve &S = a.solves[t.solve];
-        if (!tile_active(a, S, t)) continue;
-        switch (t.nr) {
-            case 1: bcgcg_update_tile<T, 1>(a, S, t, sh_red); break;
-            case 2: bcgcg_update_tile<T, 2>(a, S, t, sh_red); break;
-            case 3: bcgcg_update_tile<T, 3>(a, S, t, sh_red); break;
-            default: bcgcg_update_tile<T, 4>(a, S, t, sh_red); break;
+        int js;
+        if (!tile_field(a, S, t, SYS_RUNNING, js)) continue;
+        const size_t fs = (size_t)3 * S.g.Vh;
+        const uint32_t h = t.blk * kBlock + threadIdx.x;
+        double ps = 0.0, pc = 0.0;
+        if (h < S.g.Vh) {
+            const SysState &st = a.state[S.sys0 + js];
+            const T al = (T)st.alpha, be = (T)st.beta;
+            // the site's fifteen loads first, as in the x/r update
+            vec3<T> r = ld_v<T>(S.r, fs, S.g.Vh, js, h);
+            const vec3<T> w = ld_v<T>(S.q, fs, S.g.Vh, js, h);
+            vec3<T> p = ld_v<T>(S.p, fs, S.g.Vh, js, h);
+            vec3<T> sv = ld_v<T>(S.s, fs, S.g.Vh, js, h);
+            vec3<T> x = ld_v<T>(S.xin, fs, S.g.Vh, js, h);
+            double site = 0.0;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                p.c[c].re = r.c[c].re + be * p.c[c].re;
+                p.c[c].im = r.c[c].im + be * p.c[c].im;
+                sv.c[c].re = w.c[c].re + be * sv.c[c].re;
+                sv.c[c].im = w.c[c].im + be * sv.c[c].im;
+                x.c[c].re += al * p.c[c].re;
+                x.c[c].im += al * p.c[c].im;
+                r.c[c].re -= al * sv.c[c].re;
+                r.c[c].im -= al * sv.c[c].im;
+                site = fmat((double)r.c[c].re, (double)r.c[c].re, site);
+                site = fmat((double)r.c[c].im, (double)r.c[c].im, site);
+            }
+            st_v<T>(S.p, fs, S.g.Vh, js, h, p);
+            st_v<T>(S.s, fs, S.g.Vh, js, h, sv);
+            st_v<T>(S.xin, fs, S.g.Vh, js, h, x);
+            st_v<T>(S.r, fs, S.g.Vh, js, h, r);
+            pair_add(ps, pc, site, 0.0);
         }
+        put_tile_sum(a.partials2, S, t, js, ps, pc, sh_red);
     }
 }
 
@@ -468,22 +411,22 @@ __global__ __launch_bounds__(kBlock) void bru_accumulate_kernel(BArgs a) {
     FOR_EACH_TILE(a, ti) {
         const BTile t = a.tiles[ti];
         const BSolve &S = a.solves[t.solve];
+        int js;
+        if (!tile_field(a, S, t, SYS_RU_PENDING, js)) continue;
         const size_t fs = (size_t)3 * S.g.Vh;
         const uint32_t h = t.blk * kBlock + threadIdx.x;
-        if (h >= S.g.Vh || !tile_active(a, S, t)) continue;
-        for (int j = 0; j < t.nr; ++j) {
-            const int js = t.j0 + j;
-            if (!(a.state[S.sys0 + js].flags & SYS_RU_PENDING)) continue;
-            for (int c = 0; c < 3; ++c) {
-                const size_t i = js * fs + (size_t)c * S.g.Vh + h;
-                cpx<float> xs = ld_c<float>(S.xin, i);
-                cpx<double> xd = ld_c<double>(S.x64, i);
-                xd.re += (double)xs.re;
-                xd.im += (double)xs.im;
-                st_c<double>(S.x64, i, xd);
-                st_c<float>(S.xin, i, cpx<float>{0.0f, 0.0f});
-            }
+        if (h >= S.g.Vh) continue;
+        const vec3<float> xs = ld_v<float>(S.xin, fs, S.g.Vh, js, h);
+        vec3<double> xd = ld_v<double>(S.x64, fs, S.g.Vh, js, h);
+        vec3<float> zero;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            xd.c[c].re += (double)xs.c[c].re;
+            xd.c[c].im += (double)xs.c[c].im;
+            zero.c[c] = {0.0f, 0.0f};
         }
+        st_v<double>(S.x64, fs, S.g.Vh, js, h, xd);
+        st_v<float>(S.xin, fs, S.g.Vh, js, h, zero);
     }
 }
 
@@ -493,26 +436,24 @@ __global__ __launch_bounds__(kBlock) void bru_resume_kernel(BArgs a) {
     FOR_EACH_TILE(a, ti) {
         const BTile t = a.tiles[ti];
         const BSolve &S = a.solves[t.solve];
+        int js;
+        if (!tile_field(a, S, t, SYS_RESUME, js)) continue;
         const size_t fs = (size_t)3 * S.g.Vh;
         const uint32_t h = t.blk * kBlock + threadIdx.x;
-        if (h >= S.g.Vh || !tile_active(a, S, t)) continue;
-        for (int j = 0; j < t.nr; ++j) {
-            const int js = t.j0 + j;
-            const SysState &st = a.state[S.sys0 + js];
-            if (!(st.flags & SYS_RESUME)) continue;
-            const T be = (T)st.beta;
-            for (int c = 0; c < 3; ++c) {
-                const size_t i = js * fs + (size_t)c * S.g.Vh + h;
-                cpx<double> rd = ld_c<double>(S.r64, i);
-                cpx<T> r{(T)rd.re, (T)rd.im};
-                if (S.r != S.r64) st_c<T>(S.r, i, r);
-                if (a.skip_p) continue;
-                cpx<T> p = ld_c<T>(S.p, i);
-                p.re = r.re + be * p.re;
-                p.im = r.im + be * p.im;
-                st_c<T>(S.p, i, p);
-            }
+        if (h >= S.g.Vh) continue;
+        const T be = (T)a.state[S.sys0 + js].beta;
+        const vec3<double> rd = ld_v<double>(S.r64, fs, S.g.Vh, js, h);
+        vec3<T> r, p;
+        if (!a.skip_p) p = ld_v<T>(S.p, fs, S.g.Vh, js, h);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            r.c[c] = {(T)rd.c[c].re, (T)rd.c[c].im};
+            if (a.skip_p) continue;
+            p.c[c].re = r.c[c].re + be * p.c[c].re;
+            p.c[c].im = r.c[c].im + be * p.c[c].im;
         }
+        if (S.r != S.r64) st_v<T>(S.r, fs, S.g.Vh, js, h, r);
+        if (!a.skip_p) st_v<T>(S.p, fs, S.g.Vh, js, h, p);
     }
 }
 
@@ -666,38 +607,38 @@ int launch_bfinalize(const BArgs &a, int op, hipStream_t s) {
 
 int launch_bcg_update(const BArgs &a, int fp64, hipStream_t s) {
     if (fp64)
-        bcg_update_kernel<double><<<dim3(a.grid), kBlock, 0, s>>>(a);
+        bcg_update_kernel<double><<<dim3(a.grid, a.max_nr), kBlock, 0, s>>>(a);
     else
-        bcg_update_kernel<float><<<dim3(a.grid), kBlock, 0, s>>>(a);
+        bcg_update_kernel<float><<<dim3(a.grid, a.max_nr), kBlock, 0, s>>>(a);
     return 0;
 }
 
 int launch_bcgcg_update(const BArgs &a, int fp64, hipStream_t s) {
     if (fp64)
-        bcgcg_update_kernel<double><<<dim3(a.grid), kBlock, 0, s>>>(a);
+        bcgcg_update_kernel<double><<<dim3(a.grid, a.max_nr), kBlock, 0, s>>>(a);
     else
-        bcgcg_update_kernel<float><<<dim3(a.grid), kBlock, 0, s>>>(a);
+        bcgcg_update_kernel<float><<<dim3(a.grid, a.max_nr), kBlock, 0, s>>>(a);
     return 0;
 }
 
 int launch_bp_update(const BArgs &a, int fp64, hipStream_t s) {
     if (fp64)
-        bp_update_kernel<double><<<dim3(a.grid), kBlock, 0, s>>>(a);
+        bp_update_kernel<double><<<dim3(a.grid, a.max_nr), kBlock, 0, s>>>(a);
     else
-        bp_update_kernel<float><<<dim3(a.grid), kBlock, 0, s>>>(a);
+        bp_update_kernel<float><<<dim3(a.grid, a.max_nr), kBlock, 0, s>>>(a);
     return 0;
 }
 
 int launch_bru_accumulate(const BArgs &a, hipStream_t s) {
-    bru_accumulate_kernel<<<dim3(a.grid), kBlock, 0, s>>>(a);
+    bru_accumulate_kernel<<<dim3(a.grid, a.max_nr), kBlock, 0, s>>>(a);
     return 0;
 }
 
 int launch_bru_resume(const BArgs &a, int fp64, hipStream_t s) {
     if (fp64)
-        bru_resume_kernel<double><<<dim3(a.grid), kBlock, 0, s>>>(a);
+        bru_resume_kernel<double><<<dim3(a.grid, a.max_nr), kBlock, 0, s>>>(a);
     else
-        bru_resume_kernel<float><<<dim3(a.grid), kBlock, 0, s>>>(a);
+        bru_resume_kernel<float><<<dim3(a.grid, a.max_nr), kBlock, 0, s>>>(a);
     return 0;
 }
 

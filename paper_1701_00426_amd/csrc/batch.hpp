@@ -65,6 +65,7 @@ struct BArgs {
     uint32_t tile0;   // its first tile (the hop launches one range per tile class)
     uint32_t nsys;
     uint32_t grid;    // blocks of the launch (at most one per tile, or per tile pass)
+    uint32_t max_nr;  // most fields of any tile: the vector kernels' grid.y
     int out_parity;
     int use_hi;       // hop on the FP64 gauge field (true residual) or the inner one
     int gate_running;     // exit at once when ctl->n_running == 0

@@ -1409,6 +1409,7 @@ BArgs batch_args(const BatchPlan &B, int gate, int tile_mask) {
     a.ntiles = (uint32_t)B.tiles.size();
     a.nsys = B.nsys;
     a.grid = a.ntiles;  // one block per tile
+    for (const BClass &c : B.classes) a.max_nr = std::max(a.max_nr, (uint32_t)c.nr);
     a.gate_running = gate;
     a.tile_mask = tile_mask;
     return a;
