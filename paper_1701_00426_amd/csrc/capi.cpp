@@ -926,12 +926,18 @@ MsWork carve_ms_slots(const Geom &g, int nrhs, int nshift, int mode, int slots, 
     w.ctl = (Ctl *)c.take(sizeof(Ctl));
     w.state = (SysState *)c.take(sizeof(SysState) * (size_t)nrhs);
     w.shift = (ShiftState *)c.take(sizeof(ShiftState) * (size_t)nrhs * nshift);
-    w.steps = (ShiftStep *)c.take(sizeof(ShiftStep) * (size_t)slots * nrhs * nshift);
+    const size_t step_bytes = sizeof(ShiftStep) * (size_t)slots * nrhs * nshift;
+    // One shift and one slot (no room for more): a chunk's steps are written after its q is
+    // used and read before the next iteration writes q, and 32 bytes per field lie below
+    // the q of every chunk still to come, so they need no memory of their own.
+    const bool in_q = slots == 1 && nshift == 1;
+    w.steps = in_q ? nullptr : (ShiftStep *)c.take(step_bytes);
     w.partials = (double *)c.take(sizeof(double) * partial_count(g));
     w.p = c.take(f1);
     w.r = c.take(f1 * slots);
     w.q = c.take(f1);
     w.t = c.take(f1);
+    if (in_q) w.steps = (ShiftStep *)w.q;
     w.xs = c.take(f1 * nshift);
     w.ps = c.take(f1 * nshift);
     w.bytes = c.off;
