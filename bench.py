@@ -480,8 +480,8 @@ PAPER_TABLE4 = {(32, 32, 8, 32): (193.79, 51.80), (32, 32, 32, 8): (190.39, 51.6
                 (24, 24, 24, 24): (212.04, 53.74), (32, 32, 32, 32): (201.82, 51.72),
                 (32, 32, 32, 36): (208.54, 52.62)}
 STAPLE_LINK_BYTES = {"c128_18": 144, "c128_12": 96, "c64_12": 48, "bf16_12": 24}
-# threads per link gauge_staples takes by default (2 for FP64 links, 1 for FP32 ones)
-STAPLE_DEFAULT_THREADS = {"c128_18": 2, "c128_12": 2, "c64_12": 1, "bf16_12": 1}
+# threads per link gauge_staples takes by default from Vh = 8192 on (2 for FP64-18 links)
+STAPLE_DEFAULT_THREADS = {"c128_18": 2, "c128_12": 1, "c64_12": 1, "bf16_12": 1}
 
 
 def time_staples(stg, torch, gauges, outs, n):
