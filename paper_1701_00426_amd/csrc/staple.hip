@@ -17,15 +17,14 @@
 // neighbourhood is mostly in the XCD's L2.  Neighbour half indices come from
 // coordinate arithmetic (no index tables).  The 8 paths of each side (above /
 // below the link) share their factors:
-//   above:  X = U_nu(x+mu) U_mu(x+nu)^dag,
-//           Y = U_nu(x+mu) U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag,
-//           Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag U_mu(x+nu)^dag,
-//           W = X U_mu(x-mu+nu)^dag U_nu(x-mu)^dag,
-//   1x1: X U_nu(x)^dag;  1x2: Y U_nu(x)^dag (long side along nu), Z U_nu(x)^dag (long
-//   side forward), W U_mu(x-mu) (long side backward), so the side contributes
-//           [c0 X + c1 (Y + Z)] U_nu(x)^dag + c1 W U_mu(x-mu),
-// 11 SU(3) products instead of 14 taken path by path, 9 of them (X, Y, Z and W) chains of
-// links that need two rows only; below the link likewise
+//   above:  A = U_nu(x+mu), B = U_mu(x+nu)^dag, C = U_nu(x)^dag,
+//           Y = A U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag,
+//           Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag,
+//           W = A B U_mu(x-mu+nu)^dag U_nu(x-mu)^dag,
+//   1x1: A B C;  1x2: Y C (long side along nu), Z B C (long side forward), W U_mu(x-mu)
+//   (long side backward), so the side contributes
+//           [c1 Y + (c1 Z + c0 A) B] C + c1 W U_mu(x-mu),
+// 11 SU(3) products instead of 14 taken path by path; below the link likewise
 // with nu -> -nu.  Products accumulate in the arithmetic type of the format
 // (FP64 for complex128 links, FP32 for the 12-real FP32 / BF16 ones).
 //
@@ -400,104 +399,6 @@ struct LinkAt {
     }
 };
 
-// The first R rows of a 3x3 matrix.  A product of SU(3) links is SU(3), so two of its
-// rows give the third: chains of links are multiplied on R = 2 rows (72 fused operations
-// instead of 108, 24 registers of FP64 instead of 36) and completed at the end.  R = 3 for
-// BF16-12 links, whose rows are rounded to 8 bits and not orthonormal to FP32 (FP64-18
-// links, any matrices, take side_*_full).  32^4, staples: FP64-12 1917 -> 1590 us, FP32-12
-// 1080 -> 787, BF16-12 884 -> 857 (the FP64 kernel before issued 11 000 vector
-// instructions per link and kept the vector units 65 % busy); with the links fetched ahead
-// and the shorter row rebuild 1432, 724 and 770.  The FP32 kernels are then bound by
-// their instructions, the FP64 one (8 100 instructions per link, 1.1 ms at the 61 TFLOP/s
-// that two waves per SIMD reach) by those and the caches' 16-byte accesses together.
-template <typename T, int R>
-struct rows {
-    cpx<T> e[R][3];
-};
-
-template <int FMT>
-constexpr int chain_rows() {
-    return FMT == FMT_BF16_12 ? 3 : 2;
-}
-
-template <typename T, int R>
-__device__ __forceinline__ rows<T, R> rmul(const rows<T, R> &a, const su3<T> &b) {  // A B
-    rows<T, R> c;
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            cpx<T> t = cmul(a.e[i][0], b.e[0][j]);
-            cfma(t, a.e[i][1], b.e[1][j]);
-            cfma(t, a.e[i][2], b.e[2][j]);
-            c.e[i][j] = t;
-        }
-    return c;
-}
-
-template <typename T, int R>
-__device__ __forceinline__ rows<T, R> rmuld(const rows<T, R> &a, const su3<T> &b) {  // A B^dag
-    rows<T, R> c;
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            cpx<T> t = cmulc(b.e[j][0], a.e[i][0]);
-            cfmac(t, b.e[j][1], a.e[i][1]);
-            cfmac(t, b.e[j][2], a.e[i][2]);
-            c.e[i][j] = t;
-        }
-    return c;
-}
-
-template <typename T, int R>
-__device__ __forceinline__ rows<T, R> rows_of(const su3<T> &u) {
-    rows<T, R> r;
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) r.e[i][j] = u.e[i][j];
-    return r;
-}
-
-template <typename T, int R>
-__device__ __forceinline__ rows<T, R> rows_of_dag(const su3<T> &u) {
-    rows<T, R> r;
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) r.e[i][j] = cconj(u.e[j][i]);
-    return r;
-}
-
-// g += w times the matrix of r (R = 2: with its third row, conj(row 0 x row 1))
-template <typename T, int R>
-__device__ __forceinline__ void add_rows(su3<T> &g, T w, const rows<T, R> &r) {
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            g.e[i][j].re = fmat(w, r.e[i][j].re, g.e[i][j].re);
-            g.e[i][j].im = fmat(w, r.e[i][j].im, g.e[i][j].im);
-        }
-    if constexpr (R == 2) {
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const cpx<T> a = r.e[0][(j + 1) % 3], b = r.e[1][(j + 2) % 3];
-            const cpx<T> c = r.e[0][(j + 2) % 3], d = r.e[1][(j + 1) % 3];
-            T re = a.re * b.re, im = -a.re * b.im;  // conj(a b - c d)
-            re = fmat(-a.im, b.im, re);
-            im = fmat(-a.im, b.re, im);
-            re = fmat(-c.re, d.re, re);
-            im = fmat(c.re, d.im, im);
-            re = fmat(c.im, d.im, re);
-            im = fmat(c.im, d.re, im);
-            g.e[2][j].re = fmat(w, re, g.e[2][j].re);
-            g.e[2][j].im = fmat(w, im, g.e[2][j].im);
-        }
-    }
-}
-
 template <typename T>
 __device__ __forceinline__ void set_zero(su3<T> &c) {
 #pragma unroll
@@ -506,75 +407,101 @@ __device__ __forceinline__ void set_zero(su3<T> &c) {
         for (int j = 0; j < 3; ++j) c.e[i][j] = {T(0), T(0)};
 }
 
+template <typename T>
+__device__ __forceinline__ su3<T> dagger(const su3<T> &u) {
+    su3<T> r;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) r.e[i][j] = cconj(u.e[j][i]);
+    return r;
+}
+
 // The four paths on one side of the link (header; UP: the +nu side, else the -nu side, every
-// U_nu step reversed): acc += [c0 X + c1 (Y + Z)] C, and the path whose long side runs
-// backward, W U_mu(x-mu): with BACK its last factor, common to all sides, is left to the
-// caller and W added to back, else c1 times the path is added to acc.  Every link is
+// U_nu step reversed): acc += [c1 Y + (c1 Z + c0 A) U_mu(x+nu)^dag] C, and the path whose long
+// side runs backward, W U_mu(x-mu): with BACK its last factor, common to all sides, is left to
+// the caller and W added to back, else c1 times the path is added to acc.  Every link is
 // fetched one product or more before the one that uses it; u0 holds U_mu(x+mu) on entry
 // and is fetched again for the next side.
+//
+// The products keep all three rows.  Two rows and their cross product would do for links in
+// SU(3) (FP64-12 at 32^4 1520 us, FP32-12 766), but the links of a trajectory leave it: each
+// update rounds their rows, and a product completed that way is off by their departure.
+// Against 64-bit sums of the stored links, 8^3 x 16 in FP32-12 after 0 / 10 / 100 / 1000
+// updates: 1.2e-7 / 2.3e-7 / 6.9e-7 / 7.7e-6 with two rows, 1.3e-7 at any number with three.
+// In FP64 three rows fill the registers (256, two waves per SIMD; 40 to 70 B per lane
+// spilled): A is fetched a second time and not held, and the last factor is not shared.  32^4
+// with every link fetched where it is used (and five products more per link in FP32) / so:
+// FP64-12 1955 / 1892 us, FP32-12 1095 / 875, BF16-12 901 / 817.
 // mp1 .. n2: lexicographic displacements of x +- mu, x + 2mu, x +- nu, x +- 2nu (periodic).
 template <typename T, int FMT, bool BACK, bool UP>
 __device__ __forceinline__ void side(su3<T> &acc, su3<T> &back, RawLink<T, FMT> &u0,
                                      const LinkAt<T, FMT> &U, int mu, int nu, int mp1, int mm1,
                                      int mp2, int n1, int n2, T c0, T c1) {
-    constexpr int R = chain_rows<FMT>();
-    const auto mulu = [](const rows<T, R> &a, const su3<T> &b) {  // a step along +-nu
-        return UP ? rmul(a, b) : rmuld(a, b);
+    constexpr bool kTwice = sizeof(T) == 8;  // fetch A twice
+    const auto mulu = [](const su3<T> &a, const su3<T> &b) {  // a step along +-nu
+        return UP ? mm(a, b) : mmd(a, b);
     };
-    const auto muld = [](const rows<T, R> &a, const su3<T> &b) {  // a step along -+nu
-        return UP ? rmuld(a, b) : rmul(a, b);
+    const auto muld = [](const su3<T> &a, const su3<T> &b) {  // a step along -+nu
+        return UP ? mmd(a, b) : mm(a, b);
     };
+    const auto fetch_a = [&](RawLink<T, FMT> &r) {
+        U.fetch(r, nu, UP ? mp1 : mp1 + n1, UP ? 1 : 0);
+    };
+    const auto step = [](const RawLink<T, FMT> &r) { return UP ? r.link() : dagger(r.link()); };
     RawLink<T, FMT> p, q;
-    su3<T> g;
-    // Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag U_mu(x+nu)^dag
+    // Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag
     U.fetch(p, nu, UP ? mp2 : mp2 + n1, UP ? 0 : 1);
     U.fetch(q, mu, mp1 + n1, 0);
     fetched();
-    rows<T, R> z = rows_of<T, R>(u0.link());
-    z = mulu(z, p.link());
-    U.fetch(p, nu, UP ? mp1 : mp1 + n1, UP ? 1 : 0);
+    su3<T> z = mulu(u0.link(), p.link());
+    fetch_a(p);
     fetched();
-    z = rmuld(z, q.link());
-    // Y = U_nu(x+mu) U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag
+    z = mmd(z, q.link());
+    // Y = A U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag, A = U_nu(x+mu)
     U.fetch(q, nu, UP ? mp1 + n1 : mp1 + n2, UP ? 0 : 1);
     fetched();
-    const rows<T, R> a = UP ? rows_of<T, R>(p.link()) : rows_of_dag<T, R>(p.link());
+    su3<T> a = step(p);
     U.fetch(p, mu, n2, 0);
     fetched();
-    rows<T, R> y = mulu(a, q.link());
+    su3<T> g = mulu(a, q.link());
     U.fetch(q, nu, UP ? n1 : n2, UP ? 1 : 0);
     fetched();
-    y = rmuld(y, p.link());
+    g = mmd(g, p.link());
     U.fetch(p, mu, n1, 1);
+    if (kTwice) fetch_a(u0);
     fetched();
-    y = muld(y, q.link());
-    set_zero(g);
-    add_rows(g, c1, y);
-    rows<T, R> x;
+    g = muld(g, q.link());
+    scale(g, c1);
+    if (kTwice) a = step(u0);
+    su3<T> x;
     {
         const su3<T> b = p.link();
-        z = rmuld(z, b);
-        add_rows(g, c1, z);
+        axpby(z, c1, c0, a);
+        mmd_acc(g, z, b);
         U.fetch(q, mu, mm1 + n1, 0);
         fetched();
-        x = rmuld(a, b);  // X = U_nu(x+mu) U_mu(x+nu)^dag
+        x = mmd(a, b);
     }
+    // W = A U_mu(x+nu)^dag U_mu(x-mu+nu)^dag U_nu(x-mu)^dag
     U.fetch(p, nu, UP ? mm1 : mm1 + n1, UP ? 1 : 0);
     fetched();
-    add_rows(g, c0, x);
-    // W = X U_mu(x-mu+nu)^dag U_nu(x-mu)^dag
-    x = rmuld(x, q.link());
+    x = mmd(x, q.link());
     if constexpr (!BACK) {
         U.fetch(q, mu, mm1, 1);
         fetched();
         x = muld(x, p.link());
         U.fetch(p, nu, UP ? 0 : n1, UP ? 0 : 1);
         fetched();
-        add_rows(acc, c1, rmul(x, q.link()));
+        scale(x, c1);
+        mm_acc(acc, x, q.link());
     } else {
         U.fetch(q, nu, UP ? 0 : n1, UP ? 0 : 1);
         fetched();
-        add_rows(back, T(1), muld(x, p.link()));
+        if constexpr (UP)
+            mmd_acc(back, x, p.link());
+        else
+            mm_acc(back, x, p.link());
     }
     U.fetch(u0, mu, mp1, 1);
     fetched();
@@ -585,9 +512,8 @@ __device__ __forceinline__ void side(su3<T> &acc, su3<T> &back, RawLink<T, FMT> 
         mm_acc(acc, g, c);
 }
 
-// The same sums for FP64-18 links, any matrices: chains of three rows in FP64 hold so many
-// registers that they spill (32^4: 2250 us against 2041 us of this form), so there the
-// sides are summed as A [c0 W + c1 (U_mu(x+nu)^dag D + T U_nu(x)^dag)] + c1 E W with
+// The same sums for FP64-18 links, whose stored form takes half as many registers again
+// (32^4: 2250 us for three-row chains against 2041 us of this form), summed as A [c0 W + c1 (U_mu(x+nu)^dag D + T U_nu(x)^dag)] + c1 E W with
 //   A = U_nu(x+mu), W = U_mu(x+nu)^dag U_nu(x)^dag,
 //   D = U_mu(x-mu+nu)^dag U_nu(x-mu)^dag U_mu(x-mu),
 //   T = U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag,
@@ -651,9 +577,10 @@ void staple_kernel(StapleArgs a) {
     const uint32_t h = valid ? pencil_site(g, a.tile, j) : 0;
     const int mu = slot >> 1, P = slot & 1;
 
-    // one thread per link: the last factor of the backward paths is taken once for all six
-    // sides; two: a second sum of 9 entries would cost each wave more than it saves
-    constexpr bool kBack = TPL == 1 && FMT != FMT_C128_18;
+    // one thread per FP32 link: the last factor of the backward paths is taken once for all six
+    // sides; two threads, or FP64: a second sum of 9 entries would cost each wave more than it
+    // saves (FP64-12, one thread, 32^4: 2154 us against 1846)
+    constexpr bool kBack = TPL == 1 && sizeof(T) == 4;
     su3<T> acc, back;
     set_zero(acc);
     if (kBack) set_zero(back);

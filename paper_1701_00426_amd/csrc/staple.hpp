@@ -31,10 +31,10 @@ inline uint32_t staple_blocks(uint32_t Vh) {
 // Threads per link by default.  2 (the two sides of the link on separate waves) for
 // FP64-18 links, whose one-thread kernel needs more than 256 registers and runs one wave
 // per SIMD, and for the other formats on small lattices, where one wave per 64 links does
-// not fill the chip (one / two threads, us: 12 x 8 x 10 x 6, Vh 2880, FP64-12 25.3 / 20.5,
-// FP32-12 18.6 / 15.1, BF16-12 21.2 / 15.6; 12^4, Vh 10368, 44.7 / 45.4, 24.3 / 23.3,
-// 25.8 / 25.1; 16^3 x 8, Vh 16384, 50.1 / 56.3, 27.4 / 36.0, 29.1 / 39.4; 32^4 momentum
-// update 1763 / 1808, 886 / 1103).
+// not fill the chip (one / two threads, us: 8^4, Vh 2048, FP64-12 23.3 / 14.5, FP32-12 18.9 /
+// 12.3, BF16-12 20.2 / 12.7; 12^4, Vh 10368, 51.9 / 52.3, 24.9 / 25.4, 25.2 / 24.5; 16^4, Vh
+// 32768, 118 / 123, 57.4 / 67.4, 52.8 / 62.4; 32^4 momentum update FP64-12 2004 / 2043,
+// FP32-12 935 / 1046).
 constexpr uint32_t kStapleSplitVh = 8192;
 
 inline int staple_default_threads(int fmt, uint32_t Vh) {

@@ -1,0 +1,86 @@
+"""Staples and momentum update on links that have left SU(3): the rows that a 12-real
+format stores depart from orthonormal ones, as the rounding of every link update leaves
+them.  The reference is the FP64 sum of the plain path products of the matrices that the
+format holds (its two rows and conj(row0 x row1)).
+
+The rows depart by 2^-10, so matrix entries stay below 1 + 2^-9 and the bounds of
+test_gpu_staples.py (64 u times the weight sum, entries of paths at most 1) hold with a
+factor (1 + 2^-9)^5 < 1.02: products that take a link for unitary would be off by about
+2^-10, far above them.  The momentum update adds eps beta / 3 times the traceless Hermitian
+part of i U Sigma: one more product, and the rounding of the stored momentum (entries below
+8)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover - CPU container
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_1701_00426_amd as stg  # noqa: E402
+import seeded_inputs as si  # noqa: E402
+from oracle import oracle_np as on  # noqa: E402
+
+from gpu_common import say, to_dev  # noqa: E402
+
+UNIT = {"c128_12": 2.0 ** -53, "c64_12": 2.0 ** -24, "bf16_12": 2.0 ** -24}
+WEIGHTS = 6 * abs(on.SYMANZIK_C0) + 18 * abs(on.SYMANZIK_C1)
+BETA, EPS = 5.5, 0.02
+
+
+def _departed(dims, seed):
+    links = si.su3_links(dims, 1701, seed, sum(dims))
+    noise = si.rng(seed, 1).uniform(-1, 1, size=(2,) + links.shape)
+    return links + 2.0 ** -11 * (noise[0] + 1j * noise[1])
+
+
+def _bf16(x):
+    m, e = np.frexp(x)
+    return np.ldexp(np.rint(m * 256.0), e - 8)
+
+
+def _as_stored(links, fmt):
+    r = links[:, :2]
+    if fmt == "c64_12":
+        r = r.astype(np.complex64).astype(np.complex128)
+    elif fmt == "bf16_12":
+        r = _bf16(r.real) + 1j * _bf16(r.imag)
+    return np.concatenate([r, np.conj(np.cross(r[:, 0], r[:, 1], axis=1))[:, None]], axis=1)
+
+
+@pytest.fixture(params=[1, 2], ids=["threads-1", "threads-2"])
+def staple_threads(request):
+    key = stg._lib.STG_TUNE_STAPLE_THREADS
+    stg.stg_set_tuning(key, request.param)
+    yield request.param
+    stg.stg_set_tuning(key, 0)
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (6, 4, 2, 10)])
+@pytest.mark.parametrize("fmt", list(UNIT))
+def test_staples_of_departed_links(fmt, dims, staple_threads):
+    links = _departed(dims, 47)
+    got = stg.gauge_staples(stg.pack_gauge(dims, to_dev(links), fmt)).cpu().numpy()
+    err = float(np.max(np.abs(got - on.staples(dims, _as_stored(links, fmt)))))
+    tol = 1.02 * 64 * UNIT[fmt] * WEIGHTS
+    say(f"staples of departed links {fmt} {dims} threads={staple_threads}: {err:.2e} "
+        f"(tol {tol:.1e})")
+    assert err <= tol
+
+
+@pytest.mark.parametrize("fmt", ["c128_12", "c64_12"])
+def test_momentum_update_of_departed_links(fmt, staple_threads):
+    dims = (6, 4, 2, 10)
+    links = _departed(dims, 48)
+    mom = si.traceless_hermitian_field(dims, 48, 2)
+    cdt = np.complex64 if fmt == "c64_12" else np.complex128
+    mom = mom.astype(cdt)
+    p = to_dev(mom)
+    stg.gauge_momentum_update(stg.pack_gauge(dims, to_dev(links), fmt), p, BETA, EPS)
+    want = on.momentum_update(dims, _as_stored(links, fmt), mom.astype(np.complex128), BETA, EPS)
+    err = float(np.max(np.abs(p.cpu().numpy() - want)))
+    tol = 1.02 * 64 * UNIT[fmt] * (BETA / 3.0) * WEIGHTS * EPS + 16 * UNIT[fmt] * 8
+    say(f"momentum update of departed links {fmt} threads={staple_threads}: {err:.2e} "
+        f"(tol {tol:.1e})")
+    assert err <= tol
