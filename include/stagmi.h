@@ -344,7 +344,11 @@ typedef struct {
     int max_iter;      /* cap on operator applications of the inner iteration */
     int mode;          /* STG_CG_F64 or STG_CG_MIXED */
     double delta;      /* reliable update when |r| < delta * max|r| since the last one (0.1) */
-    int poll_every;    /* iterations enqueued between host convergence checks (0: auto) */
+    int poll_every;    /* iterations enqueued between host convergence checks (0: auto).
+                          A system that is due for a true-residual update waits for the
+                          check after next at most; mixed solves on small lattices take
+                          it without the host at the end of every run of 8 iterations or
+                          more */
     int restart;       /* 1: restart p = r at each reliable update, 0: keep p, -1: auto
                           (restart when the lo gauge field is BF16-12, else keep p) */
 } stg_cg_params;
@@ -563,10 +567,10 @@ int stg_batch_workspace_bytes(int nsolve, const stg_solve_desc *descs, int mode,
 
 /*
  * Solves every system of every descriptor.  params->poll_every is the number of
- * iterations per graph replay (0: 8 for small batches, whose replays end with the
- * true-residual update of the parked systems, else 16).  stats (host) receives one entry
- * per system, descriptors in order and RHS in order within each.  Returns STG_OK when
- * every system converged, else the worst status.
+ * iterations per graph replay (0: 8 for small batches, else 16).  Replays of 8 or more
+ * iterations of a small batch end with the true-residual update of the parked systems.
+ * stats (host) receives one entry per system, descriptors in order and RHS in order within
+ * each.  Returns STG_OK when every system converged, else the worst status.
  */
 int cg_solve_batch(int nsolve, const stg_solve_desc *descs, const stg_cg_params *params, void *ws,
                    size_t ws_bytes, stg_cg_stats *stats, stg_stream_t stream);

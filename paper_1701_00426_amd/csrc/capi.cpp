@@ -21,6 +21,7 @@
 #include "batch.hpp"
 #include "force.hpp"
 #include "kernels.hpp"
+#include "runs.hpp"
 #include "solver_state.hpp"
 #include "staple.hpp"
 #include "tune.hpp"
@@ -659,34 +660,10 @@ int read_states(const CgWork &w, int nsys, std::vector<SysState> &st, hipStream_
     return read_states_n(w.state, nsys, st, s);
 }
 
-// Whether every run of iterations ends with the true-residual update, queued without a
-// look at the flags (its kernels leave at once when no system is parked): mixed solves on
-// small lattices, whose systems park every few dozen iterations.  Left to the host, each
-// update waited for up to two runs of iterations that had nothing to do, 7 us each: 311
-// iterations of 4^4 with 11 updates took 14.3 ms with runs of 64 iterations and take 5.4;
-// 16^4 with BF16-12 links 23.5 and 10.1; 8^4 with 4 RHS 28.5 and 11.3.
-// On larger lattices the five idle launches cost more than the wait.
-bool inline_update(const CgProblem &P, int live) {
-    return P.mode == STG_CG_MIXED && (P.group == 0 || P.group == P.nsys) &&
-           (uint64_t)P.g.Vh * (uint64_t)live <= (1u << 17);
-}
-
-// Iterations queued between two looks at the flags.  A look costs a copy of a few bytes
-// (4 us on the stream); a system that has parked or converged waits for one to two runs.
-// Small lattices: 12 with the update in the run, else 8 (mixed) or 16 (FP64, where only
-// the end of a system waits); a large one about 4 million site updates, at least 8.
-// Several systems share launches that go on with their fields while they wait, so there a
-// run is 2 million site-field updates, at least 2 iterations (16 shifts x 2 RHS at 24^3 x
-// 48: 328 ms with at least 4 and twice the work, 324 so; 16^4, 12 x 3: 52.0 and 49.1).
-int poll_iterations(const CgProblem &P, int live) {
-    if (P.prm.poll_every > 0) return P.prm.poll_every;
-    if (inline_update(P, live)) return 12;
-    const uint32_t most = P.mode == STG_CG_MIXED ? 8 : 16;
-    if (live > 1) {
-        const uint32_t work = (1u << 21) / P.g.Vh / (uint32_t)live;
-        return (int)std::min<uint32_t>(most, std::max<uint32_t>(2, work));
-    }
-    return (int)std::min<uint32_t>(most, std::max<uint32_t>(8, (1u << 22) / P.g.Vh));
+bool update_in_run(const CgProblem &P, int live) {
+    return queued_update(P.prm.poll_every,
+                         P.mode == STG_CG_MIXED && (P.group == 0 || P.group == P.nsys),
+                         (uint64_t)P.g.Vh * (uint64_t)live);
 }
 
 int run_cg(const CgProblem &P, CgWork w, stg_cg_stats *stats, hipStream_t s) {
@@ -763,7 +740,7 @@ int run_cg(const CgProblem &P, CgWork w, stg_cg_stats *stats, hipStream_t s) {
     for (;;) {
         int running = 0, pending = 0, live = 0;
         for (int j = 0; j < n; ++j) live += system_live(st[j]) ? 1 : 0;
-        const bool with_update = inline_update(P, live);
+        const bool with_update = update_in_run(P, live);
         for (int j = 0; j < n; ++j) {
             if (with_update) {
                 running += system_live(st[j]) ? 1 : 0;
@@ -807,7 +784,8 @@ int run_cg(const CgProblem &P, CgWork w, stg_cg_stats *stats, hipStream_t s) {
             if (rc) return rc;
         }
         const std::vector<Chunk> chunks = live_chunks(P, st);
-        const int poll = poll_iterations(P, live);
+        const int poll =
+            run_iterations(P.prm.poll_every, with_update, P.mode == STG_CG_MIXED, P.g.Vh, live);
         for (int i = 0; i < poll; ++i) {
             rc = enqueue_inner_iteration(P, w, chunks, s);
             if (rc) return rc;
@@ -1124,7 +1102,7 @@ int run_mscg(const Geom &g, const stg_gauge *hi, const stg_gauge *lo, double mas
                                s));
     }
     int poll = prm.poll_every;
-    // as in poll_iterations: on a small lattice up to two runs are idle after the last step
+    // as in run_iterations: on a small lattice up to two runs are idle after the last step
     if (poll <= 0) poll = (int)std::min<uint32_t>(16, std::max<uint32_t>(8, (1u << 22) / g.Vh));
     rc = snapshots_ready(nrhs);
     if (rc) return rc;
@@ -1483,25 +1461,17 @@ int enqueue_batch_update(const BatchPlan &B, int f64, int fmt_hi, hipStream_t s)
 
 thread_local hipStream_t g_capture_stream = nullptr;
 
-// Small batches (all tiles' hop passes in one merged launch, batch.hpp) end every replay
-// with the true-residual update of the systems parked by then.  Its kernels leave the
-// tiles without a parked system alone, so a replay that parks none pays for five launches,
-// and a parked system waits for the end of its replay; with the update launched by the
-// host it waits for the next replay too, and the update drains the stream (16 solves of
-// 8^4 to 16^4: 816 iterations of the batch instead of about 660).  Large batches keep the
-// host's update: there the five launches over every tile cost 1 % (1.250 s against 1.238
-// for 12 solves up to 32^4) and the wait is hidden by the other solves.
-bool batch_inline_update(const BatchPlan &B) { return 4 * B.tiles.size() <= kMergeBlocks; }
+bool small_batch(const BatchPlan &B) { return 4 * B.tiles.size() <= kMergeBlocks; }
 
-// K inner iterations of the whole batch (and the update), captured into one executable
-// graph.
-int capture_batch(const BatchPlan &B, int f64, int fmt_in, int fmt_hi, int K, hipGraph_t &graph,
-                  hipGraphExec_t &exec) {
+// K inner iterations of the whole batch, with `update` followed by the true-residual update,
+// captured into one executable graph.
+int capture_batch(const BatchPlan &B, int f64, int fmt_in, int fmt_hi, int K, bool update,
+                  hipGraph_t &graph, hipGraphExec_t &exec) {
     graph = nullptr;
     exec = nullptr;
     if (!g_capture_stream) HIP_TRY(hipStreamCreateWithFlags(&g_capture_stream, hipStreamNonBlocking));
     HIP_TRY(hipStreamBeginCapture(g_capture_stream, hipStreamCaptureModeThreadLocal));
-    const int parts = K + (batch_inline_update(B) ? 1 : 0);
+    const int parts = K + (update ? 1 : 0);
     for (int i = 0; i < parts; ++i) {
         const int rc = i < K ? enqueue_batch_iteration(B, f64, fmt_in, g_capture_stream)
                              : enqueue_batch_update(B, f64, fmt_hi, g_capture_stream);
@@ -1522,9 +1492,6 @@ int capture_batch(const BatchPlan &B, int f64, int fmt_in, int fmt_hi, int K, hi
     }
     return STG_OK;
 }
-
-// Iterations per replay of the batch's graph when the caller leaves them open.
-int batch_replay(const BatchPlan &B) { return batch_inline_update(B) ? 8 : 16; }
 
 int run_cg_batch(int nsolve, const stg_solve_desc *d, const stg_cg_params &prm, void *ws,
                  stg_cg_stats *stats, hipStream_t s) {
@@ -1602,11 +1569,11 @@ int run_cg_batch(int nsolve, const stg_solve_desc *d, const stg_cg_params &prm, 
 
     // K inner iterations of the whole batch, captured and replayed; captured again
     // over the remaining tiles when finished solves leave enough of them idle
-    int K = prm.poll_every > 0 ? prm.poll_every : batch_replay(B);
-    bool inline_update = batch_inline_update(B);
+    int K = batch_run(prm.poll_every, small_batch(B));
+    bool with_update = batch_queued_update(K, small_batch(B));
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    rc = capture_batch(B, f64, fmt_in, fmt_hi, K, graph, exec);
+    rc = capture_batch(B, f64, fmt_in, fmt_hi, K, with_update, graph, exec);
     if (rc) return rc;
     int replays = 0;
     rc = snapshots_ready(n);
@@ -1619,7 +1586,7 @@ int run_cg_batch(int nsolve, const stg_solve_desc *d, const stg_cg_params &prm, 
             if (st[k].flags & SYS_RUNNING) ++running;
             if (st[k].flags & SYS_RU_PENDING) ++pending;
         }
-        if (pending && !inline_update) {
+        if (pending && !with_update) {
             if (pend >= 0) {
                 rc = snapshot_wait(n, pend, st);
                 if (rc) break;
@@ -1656,9 +1623,9 @@ int run_cg_batch(int nsolve, const stg_solve_desc *d, const stg_cg_params &prm, 
             }
             (void)hipGraphExecDestroy(exec);
             (void)hipGraphDestroy(graph);
-            if (prm.poll_every <= 0) K = batch_replay(B);
-            inline_update = batch_inline_update(B);
-            rc = capture_batch(B, f64, fmt_in, fmt_hi, K, graph, exec);
+            K = batch_run(prm.poll_every, small_batch(B));
+            with_update = batch_queued_update(K, small_batch(B));
+            rc = capture_batch(B, f64, fmt_in, fmt_hi, K, with_update, graph, exec);
             if (rc) break;
         }
         hipError_t le = hipGraphLaunch(exec, s);
