@@ -174,7 +174,8 @@ const char *stg_last_error(void);
  *     with LDS neighbour staging.  It changes which sites share a block, so the
  *     order of additions in the reductions (not the operator) may change.  With 0,
  *     launches that take the field split automatically (STG_TUNE_FIELD_SPLIT) use
- *     G = 4 above Vh = 65536.
+ *     G = 4 above Vh = 65536, and for 8 fields with FP64-12 links also from Vh = 14337 to
+ *     16384.
  *   STG_TUNE_SPREAD_EPILOGUE: 0 (default) or 1: with 2 or 4 threads per site and a
  *     number of fields per launch that is a multiple of it, every thread group adds
  *     the partial sums of its share of the fields and runs their epilogue (the
@@ -187,10 +188,10 @@ const char *stg_last_error(void);
  *     and the block reads its sites' links from memory once into LDS, where every
  *     wave reads them.  F takes precedence over STG_TUNE_THREADS_PER_SITE for such
  *     launches.  Automatic, when STG_TUNE_THREADS_PER_SITE is automatic too: launches
- *     of 8 fields take F = 2 with FP64-12 links and, with FP32-12 / BF16-12 links, F = 1
- *     up to Vh = 65536 and F = 2 above; launches of 4 fields take F = 1 with FP64-12 links
- *     from Vh = 8192 on and with FP32-12 / BF16-12 links up to Vh = 65536; other launches
- *     keep the threads per site.  It changes the order of
+ *     of 8 fields take F = 1 up to Vh = 16384 with FP64-12 links and up to Vh = 65536 with
+ *     FP32-12 / BF16-12 links, F = 2 above; launches of 4 fields take F = 1 above Vh = 16384
+ *     with FP64-12 links and from Vh = 8192 up to 65536 with FP32-12 / BF16-12 links; other
+ *     launches keep the threads per site.  It changes the order of
  *     additions, so results may differ in the last bits.
  *   STG_TUNE_CG_FORM: 0 (default: automatic: form 2 for a solve of one field, else
  *     form 1), 1 or 2: the form of

@@ -157,7 +157,7 @@ int launch_hop(const HopArgs &a, int fmt, int nr, int epi, hipStream_t stream) {
     if (fpw > 0 && nr >= 2) {
         HopArgs b = a;
         b.fields_per_wave = fpw;
-        if (automatic && b.layer_group == 0 && a.geom.Vh > kFieldSplitSmallVh)
+        if (automatic && b.layer_group == 0 && default_layer_order(fmt, nr, a.geom.Vh))
             b.layer_group = a.layer_group_auto;
         const int rc = launch_hop_fsplit(b, fmt, nr, epi, stream);
         if (rc != -1) return rc;  // launched, or refused for lack of partials

@@ -178,29 +178,44 @@ int launch_hop_fsplit(const HopArgs &a, int fmt, int nr, int epi, hipStream_t st
 // Fields per wave of the field-split hop when the caller leaves both it and the
 // threads per site open (0: the direction-split hop).  Plain / normal-operator times in
 // us on MI355X, 8 fields:
-//   FP64-12: 2 fields per wave (32^4 158.6 / 391 against 182.7 / 412 with one, 20^4 28.2 /
-//     62.7 and 30.7 / 67.4, 8^4 6.0 / 13.0 and 6.1 / 13.0): a wave decodes the link of a
-//     site once for two mat-vecs;
+//   FP64-12: 2 fields per wave above Vh = 16384 (32^4 158.6 / 391 against 182.7 / 412 with
+//     one, 20^4 28.2 / 62.7 and 30.7 / 67.4): a wave decodes the link of a site once for two
+//     mat-vecs; 1 up to there, where every 64-site block has a CU of its own and twice the
+//     waves hide more of the latency (12^4 7.1 / 15.6 against 7.0 / 16.0, 14400 half sites
+//     7.3 / 17.6 and 7.2 / 19.1, 16^3 x 8 7.4 / 17.3 and 7.4 / 21.1; 20 x 14 x 10 x 12, Vh
+//     16800, 9.7 / 22.2 and 9.2 / 22.0; 8^4 6.1 / 12.7 and 5.9 / 12.8);
 //   FP32-12, BF16-12: 2 on large lattices (32^4 90.4 / 196 against 90.5 / 199 with one),
-//     1 up to Vh = 65536, where twice the waves hide more of the latency (16^3 x 32
+//     1 up to Vh = 65536, for the same reason (16^3 x 32
 //     FP32-12 13.3 / 28.4 against 14.7 / 30.5, 8^4 9.1 against 11.0; 20^4 39.3 and 39.2).
 // 4 fields:
-//   FP64-12: 1 from Vh = 8192 on (24^3 x 48 76.8 / 163 against 85.0 / 179 with 4 threads
-//     per site, 12^4 6.0 / 11.8 and 6.3 / 12.2; 8^4 10.4 and 9.9);
-//   FP32-12, BF16-12: 1 up to Vh = 65536 (16^3 x 32 19.5 against 20.6 and 16.7 against
-//     18.1; 20^4 27.0 and 25.6, 23.9 and 23.4).
-// Automatic launches above Vh = 65536 also take the layer order with 4 x3 planes per group
-// unless the caller set an order (HopArgs::layer_group_auto): below, the fields of the
-// planes in flight fit the L2s in half-index order too (16^3 x 32, 8 FP64 fields 53.8
-// against 55.7 with it; 20^4 65.1 and 62.7, 32^4 426 and 391).
+//   FP64-12: 1 above Vh = 16384 (24^3 x 48 76.8 / 163 against 85.0 / 179 with 4 threads
+//     per site, 16^3 x 12 7.7 / 17.7 and 8.4 / 18.0; 12^4 6.2 / 12.1 and 6.4 / 11.6, with
+//     stored phases 6.5 / 12.7 and 6.6 / 11.7; 8^4 6.2 / 10.9 and 6.3 / 10.5);
+//   FP32-12, BF16-12: 1 from Vh = 8192 up to 65536 (16^3 x 32 19.5 against 20.6 and 16.7
+//     against 18.1, 16^3 x 8 10.1 and 10.6; 8^3 x 16 9.9 and 9.3; 20^4 27.0 and 25.6, 23.9 and
+//     23.4).
 constexpr uint32_t kFieldSplitSmallVh = 65536;
+constexpr uint32_t kFieldSplitRoundVh = 16384;  // 64-site blocks of 256 CUs
 
 inline int default_fields_per_wave(int fmt, int nr, uint32_t Vh) {
     const bool small = Vh <= kFieldSplitSmallVh;
-    if (fmt == FMT_C128_12) return nr == 8 ? 2 : (nr == 4 && Vh >= 8192) ? 1 : 0;
+    const bool one_round = Vh <= kFieldSplitRoundVh;
+    if (fmt == FMT_C128_12) return nr == 8 ? (one_round ? 1 : 2) : (nr == 4 && !one_round) ? 1 : 0;
     if (fmt != FMT_C64_12 && fmt != FMT_BF16_12) return 0;
     if (nr == 8) return small ? 1 : 2;
-    return (nr == 4 && small) ? 1 : 0;
+    return (nr == 4 && small && Vh >= 8192) ? 1 : 0;
+}
+
+// Whether such an automatic launch takes the layer order with 4 x3 planes per group when
+// the caller sets no order (HopArgs::layer_group_auto): above Vh = 65536, where the fields of
+// the planes in flight no longer fit the L2s in half-index order (16^3 x 32, 8 FP64 fields
+// 53.8 us against 55.7 with it; 20^4 65.1 and 62.7, 32^4 426 and 391), and for 8 FP64 fields
+// in one round of blocks whose links and fields just fill them (Vh 14400 18.3 against 17.6,
+// 16^3 x 8 20.0 and 17.3, 8 x 16^3 16.9 and 16.3; Vh 13824 15.9 and 16.2).
+inline bool default_layer_order(int fmt, int nr, uint32_t Vh) {
+    if (Vh > kFieldSplitSmallVh) return true;
+    return fmt == FMT_C128_12 && nr == 8 && Vh <= kFieldSplitRoundVh &&
+           Vh > kFieldSplitRoundVh / 8 * 7;
 }
 
 // Threads per site when the caller leaves the choice open, from hop timings at 32^4
