@@ -18,7 +18,6 @@ phases float64 (8, Vh) or None for the standard staggered phases, fields
 from __future__ import annotations
 
 import ctypes
-import functools
 from dataclasses import dataclass
 from typing import Optional
 
@@ -78,10 +77,23 @@ def _ptr(t: Optional[torch.Tensor]):
     return t.data_ptr()
 
 
-@functools.lru_cache(maxsize=256)
+_lattices = {}  # extents as ints -> _lattice_of
+
+
 def _lattice_of(dims: tuple):
-    """(pointer argument, half volume) of the extents."""
-    return ctypes.byref(_lib.lattice(dims)), half_volume(dims)
+    """(pointer argument, half volume) of the extents.  Only tuples of ints are kept: other
+    forms may change under the same object or have no hash."""
+    try:
+        hit = _lattices.get(dims)
+    except TypeError:
+        hit = None
+    if hit is None:
+        dims = tuple(int(d) for d in dims)
+        hit = ctypes.byref(_lib.lattice(dims)), half_volume(dims)
+        if len(_lattices) >= 256:
+            _lattices.clear()
+        _lattices[dims] = hit
+    return hit
 
 
 def _lat(dims):
