@@ -294,11 +294,12 @@ def bench_multishift():
     print(json.dumps(out), flush=True)
 
 
-def multishift_stage_bytes(dims, stats, elem):
+def multishift_stage_bytes(dims, stats, elem, slots=8):
     """Algorithmic bytes of the multi-shift stage (each datum once per kernel), from
     the iterations each (shift, RHS) system took part in (stats[k][j]["ms_iters"]):
     the operator (two hops per iteration; one link read per launch serves the 8
-    fields of a launch) against the vector kernels, the shift update above all.
+    fields of a launch) against the vector kernels.  The shifted vectors are updated
+    once for `slots` iterations, from a ring of that many base residuals.
     elem: bytes per complex entry of the stage's vectors (8 for FP32)."""
     vh = 1
     for d in dims:
@@ -311,15 +312,19 @@ def multishift_stage_bytes(dims, stats, elem):
     launches = sum(max(base[j0:j0 + 8]) for j0 in range(0, nrhs, 8))   # 8 fields per launch
     link_bytes = 8 * 6 * elem                      # FP32-12: 48 B per link, 8 per site
     hops = vh * (2 * launches * link_bytes + sum(base) * (2 * vec + 3 * vec))
-    r_update = vh * sum(base) * 3 * vec            # r, q read, r written
-    # base p: r, p read, p written; each (shift, RHS) still in the stage: p_k, x_k read,
-    # x_k and p_k written (r is re-read by every shift's blocks from L2: counted once)
-    p_update = vh * (sum(base) * 3 * vec + shift_iters * 4 * vec)
+    r_update = vh * sum(base) * 3 * vec            # r, q read, the next r written
+    p_update = vh * sum(base) * 3 * vec            # base p: r, p read, p written
+    # each (shift, RHS) of a ring: p_k, x_k read and written; the ring's residuals are
+    # re-read by every shift's blocks from L2: counted once
+    rings = sum(-(-stats[k][j]["ms_iters"] // slots) for k in range(nshift) for j in range(nrhs))
+    shift_update = vh * (sum(base) * vec + rings * 4 * vec)
     return {"hop_launch_pairs": launches, "base_iters": base, "shift_iters_total": shift_iters,
-            "hops": hops, "ms_r_update": r_update, "ms_p_update": p_update,
+            "hops": hops, "ms_r_update": r_update, "p_update": p_update,
+            "ms_shift_update": shift_update,
             "model": "hops: 2 x 8 links x 48 B per launch + per field 2 x (in + out) + p; "
-                     "ms_r_update: 3 vectors per field; ms_p_update: 3 vectors per field + "
-                     "4 vectors per (shift, RHS) iteration; vector = 24 B per site"}
+                     "ms_r_update: 3 vectors per field; p_update: 3 vectors per field; "
+                     f"ms_shift_update: 1 vector per field + 4 vectors per (shift, RHS) and "
+                     f"{slots} iterations; vector = {vec} B per site"}
 
 
 def bench_rational():
