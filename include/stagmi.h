@@ -149,8 +149,10 @@ const char *stg_last_error(void);
  *     between choices (each choice is deterministic).
  *   STG_TUNE_STAPLE_THREADS: 0 (default: automatic), 1 or 2 threads per link in
  *     gauge_staples; with 2 the paths above and below the link run on separate
- *     waves and meet in LDS.  Automatic: 2 for FP64-18 links and on lattices
- *     with Vh < 8192, else 1.  Like the threads per site, it changes the order of additions.
+ *     waves and meet in LDS.  Automatic: 2 for FP64-18 links, for FP64-12 ones on
+ *     lattices with Vh <= 4096 or 8192 < Vh <= 12288, and for FP32-12 and BF16-12 ones
+ *     up to Vh = 12288; else 1.  Like the threads per site, it changes the order of
+ *     additions.
  *     STG_TUNE_XCD_REMAP applies to gauge_staples too.
  *   STG_TUNE_PENCIL_TILE: 0 (default) .. 5: the tile of the order in which
  *     gauge_staples, stout_smear and fermion_force visit the sites: tiles of

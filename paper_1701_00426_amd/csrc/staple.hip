@@ -425,43 +425,38 @@ __device__ __forceinline__ su3<T> dagger(const su3<T> &u) {
 // and is fetched again for the next side.
 //
 // The products keep all three rows.  Two rows and their cross product would do for links in
-// SU(3) (FP64-12 at 32^4 1520 us, FP32-12 766), but the links of a trajectory leave it: each
+// SU(3) (FP64-12 at 32^4 1490 us, FP32-12 752), but the links of a trajectory leave it: each
 // update rounds their rows, and a product completed that way is off by their departure.
 // Against 64-bit sums of the stored links, 8^3 x 16 in FP32-12 after 0 / 10 / 100 / 1000
 // updates: 1.2e-7 / 2.3e-7 / 6.9e-7 / 7.7e-6 with two rows, 1.3e-7 at any number with three.
-// In FP64 three rows fill the registers (256, two waves per SIMD; 40 to 70 B per lane
-// spilled): A is fetched a second time and not held, and the last factor is not shared.  32^4
-// with every link fetched where it is used (and five products more per link in FP32) / so:
-// FP64-12 1955 / 1892 us, FP32-12 1095 / 875, BF16-12 901 / 817.
+// 32^4 with every link fetched where it is used (11 products, FP64-12 on two threads) / so:
+// FP64-12 1929 / 1707 us, FP32-12 1068 / 857, BF16-12 880 / 791.  In FP64 the matrices take
+// 310 registers and one wave runs per SIMD; held to two, it spills 248 B per lane (2500 us),
+// and with a matrix fetched twice and the last factor of every side multiplied 60 B (1815).
 // mp1 .. n2: lexicographic displacements of x +- mu, x + 2mu, x +- nu, x +- 2nu (periodic).
 template <typename T, int FMT, bool BACK, bool UP>
 __device__ __forceinline__ void side(su3<T> &acc, su3<T> &back, RawLink<T, FMT> &u0,
                                      const LinkAt<T, FMT> &U, int mu, int nu, int mp1, int mm1,
                                      int mp2, int n1, int n2, T c0, T c1) {
-    constexpr bool kTwice = sizeof(T) == 8;  // fetch A twice
     const auto mulu = [](const su3<T> &a, const su3<T> &b) {  // a step along +-nu
         return UP ? mm(a, b) : mmd(a, b);
     };
     const auto muld = [](const su3<T> &a, const su3<T> &b) {  // a step along -+nu
         return UP ? mmd(a, b) : mm(a, b);
     };
-    const auto fetch_a = [&](RawLink<T, FMT> &r) {
-        U.fetch(r, nu, UP ? mp1 : mp1 + n1, UP ? 1 : 0);
-    };
-    const auto step = [](const RawLink<T, FMT> &r) { return UP ? r.link() : dagger(r.link()); };
     RawLink<T, FMT> p, q;
     // Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag
     U.fetch(p, nu, UP ? mp2 : mp2 + n1, UP ? 0 : 1);
     U.fetch(q, mu, mp1 + n1, 0);
     fetched();
     su3<T> z = mulu(u0.link(), p.link());
-    fetch_a(p);
+    U.fetch(p, nu, UP ? mp1 : mp1 + n1, UP ? 1 : 0);
     fetched();
     z = mmd(z, q.link());
     // Y = A U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag, A = U_nu(x+mu)
     U.fetch(q, nu, UP ? mp1 + n1 : mp1 + n2, UP ? 0 : 1);
     fetched();
-    su3<T> a = step(p);
+    const su3<T> a = UP ? p.link() : dagger(p.link());
     U.fetch(p, mu, n2, 0);
     fetched();
     su3<T> g = mulu(a, q.link());
@@ -469,11 +464,9 @@ __device__ __forceinline__ void side(su3<T> &acc, su3<T> &back, RawLink<T, FMT> 
     fetched();
     g = mmd(g, p.link());
     U.fetch(p, mu, n1, 1);
-    if (kTwice) fetch_a(u0);
     fetched();
     g = muld(g, q.link());
     scale(g, c1);
-    if (kTwice) a = step(u0);
     su3<T> x;
     {
         const su3<T> b = p.link();
@@ -555,16 +548,16 @@ __device__ __forceinline__ void side_below_full(su3<T> &acc, const LinkAt<T, FMT
 
 // TPL threads per link (1 or 2): a block is TPL waves over the same kStapleLinks
 // links; with 2, wave 0 sums the +nu sides and wave 1 the -nu sides, and wave 0
-// adds wave 1's sums from LDS.  Two waves per SIMD (256 registers) are asked of the FP64
-// kernels, but not of the one-thread FP64-18 one, which would spill 248 bytes (2049 ->
-// 3107 us at 32^4).
+// adds wave 1's sums from LDS.  Two waves per SIMD (256 registers) are asked of the
+// two-thread FP64-18 kernel only: the one-thread one would spill 248 bytes (2049 -> 3107 us
+// at 32^4), the FP64-12 ones lose more than they gain (comment at side()).
 // EPI 0 writes Sigma; EPI 1 (FP64 or FP32-12 links) instead adds (eps beta / 3) times the
 // traceless Hermitian part of i U Sigma to the link's momentum: P -> P - eps F with the
 // Symanzik gauge force F = -(beta/3) [i U Sigma]_TH, the staples never leaving the
 // kernel.
 template <typename T, int FMT, int TPL, int EPI>
 __global__ __launch_bounds__(kStapleLinks * TPL)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && (TPL == 2 || FMT != FMT_C128_18) ? 2 : 1)))
+__attribute__((amdgpu_waves_per_eu(FMT == FMT_C128_18 && TPL == 2 ? 2 : 1)))
 void staple_kernel(StapleArgs a) {
     __shared__ cpx<T> part[9][kStapleLinks];
     const Geom &g = a.geom;
@@ -577,10 +570,9 @@ void staple_kernel(StapleArgs a) {
     const uint32_t h = valid ? pencil_site(g, a.tile, j) : 0;
     const int mu = slot >> 1, P = slot & 1;
 
-    // one thread per FP32 link: the last factor of the backward paths is taken once for all six
-    // sides; two threads, or FP64: a second sum of 9 entries would cost each wave more than it
-    // saves (FP64-12, one thread, 32^4: 2154 us against 1846)
-    constexpr bool kBack = TPL == 1 && sizeof(T) == 4;
+    // one thread per link: the last factor of the backward paths is taken once for all six
+    // sides; two: a second sum of 9 entries would cost each wave more than it saves
+    constexpr bool kBack = TPL == 1 && FMT != FMT_C128_18;
     su3<T> acc, back;
     set_zero(acc);
     if (kBack) set_zero(back);

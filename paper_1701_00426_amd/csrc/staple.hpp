@@ -30,15 +30,21 @@ inline uint32_t staple_blocks(uint32_t Vh) {
 
 // Threads per link by default.  2 (the two sides of the link on separate waves) for
 // FP64-18 links, whose one-thread kernel needs more than 256 registers and runs one wave
-// per SIMD, and for the other formats on small lattices, where one wave per 64 links does
-// not fill the chip (one / two threads, us: 8^4, Vh 2048, FP64-12 23.3 / 14.5, FP32-12 18.9 /
-// 12.3, BF16-12 20.2 / 12.7; 12^4, Vh 10368, 51.9 / 52.3, 24.9 / 25.4, 25.2 / 24.5; 16^4, Vh
-// 32768, 118 / 123, 57.4 / 67.4, 52.8 / 62.4; 32^4 momentum update FP64-12 2004 / 2043,
-// FP32-12 935 / 1046).
-constexpr uint32_t kStapleSplitVh = 8192;
-
+// per SIMD, and for the other formats where it fills the chip better.
+//   FP64-12: one wave per SIMD, 1024 at a time, and a round of two-thread waves takes about
+//   0.6 of one of one-thread waves: 2 where that makes the rounds shorter (one / two threads,
+//   us: Vh 4096 22.2 / 16.3, 4608 22.2 / 27.3, 8192 26.6 / 29.0, 8640 46.6 / 42.2, 12288 46.5 /
+//   43.7, 13824 51.6 / 57.8, 16384 52.7 / 59.8, 18432 70.7 / 70.2, 20480 71.1 / 75.2; 32^4
+//   1707 / 1900);
+//   FP32-12, BF16-12: up to Vh = 12288, where one wave per 64 links does not fill the chip (Vh
+//   4096 19.9 / 14.4 and 21.0 / 14.9, 8192 20.2 / 17.0 and 21.3 / 16.6, 12288 25.2 / 25.0 and
+//   25.5 / 24.1, 13824 27.5 / 32.7 and 25.9 / 29.8; 32^4 857 / 947 and 791 / 879).
 inline int staple_default_threads(int fmt, uint32_t Vh) {
-    return (fmt == FMT_C128_18 || Vh < kStapleSplitVh) ? 2 : 1;
+    if (fmt == FMT_C128_18) return 2;
+    if (fmt != FMT_C128_12) return Vh <= 12288 ? 2 : 1;
+    const uint32_t waves = staple_blocks(Vh), round = 1024;
+    const uint32_t one = (waves + round - 1) / round, two = (2 * waves + round - 1) / round;
+    return 3 * two < 5 * one ? 2 : 1;
 }
 
 // 0: launched; -1: unknown format or thread count (nothing launched).

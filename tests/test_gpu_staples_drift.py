@@ -49,6 +49,28 @@ def _as_stored(links, fmt):
     return np.concatenate([r, np.conj(np.cross(r[:, 0], r[:, 1], axis=1))[:, None]], axis=1)
 
 
+@pytest.mark.parametrize("fmt,dims,threads", [
+    ("c128_12", (8, 8, 8, 16), 2), ("c128_12", (12, 12, 8, 8), 1), ("c128_12", (16, 16, 8, 8), 1),
+    ("c128_12", (12, 12, 12, 10), 2), ("c128_12", (16, 16, 16, 6), 2),
+    ("c128_12", (12, 12, 12, 16), 1), ("c128_18", (12, 12, 12, 16), 2),
+    ("c64_12", (16, 16, 16, 6), 2), ("c64_12", (12, 12, 12, 16), 1),
+    ("bf16_12", (16, 16, 16, 6), 2), ("bf16_12", (12, 12, 12, 16), 1)])
+def test_automatic_threads(fmt, dims, threads):
+    # the two add in different orders, so some last bits differ; the automatic choice is bitwise
+    # the one expected
+    g = stg.pack_gauge(dims, to_dev(si.su3_links(dims, 1701, 49, 0)), fmt)
+    key = stg._lib.STG_TUNE_STAPLE_THREADS
+    out = {}
+    for n in (0, 1, 2):
+        stg.stg_set_tuning(key, n)
+        try:
+            out[n] = stg.gauge_staples(g)
+        finally:
+            stg.stg_set_tuning(key, 0)
+    assert torch.equal(out[0], out[threads])
+    assert not torch.equal(out[0], out[3 - threads])
+
+
 @pytest.fixture(params=[1, 2], ids=["threads-1", "threads-2"])
 def staple_threads(request):
     key = stg._lib.STG_TUNE_STAPLE_THREADS
