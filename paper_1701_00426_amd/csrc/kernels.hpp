@@ -254,7 +254,9 @@ struct VecArgs {
     SysState *state;
     Ctl *ctl;
     double *partials;
-    int gate_mask;        // as in HopArgs; the fused single-field kernels gate on ctl->n_running
+    int gate_mask;        // as in HopArgs, per field; the fused single-field kernels of the classic
+                          // form gate on ctl->n_running, of the single-reduction form on the
+                          // system's flags
     int op;
     // multi-shift: shifted solutions and directions, [nshift][nrhs][3][Vh]
     void *xs;

@@ -8,9 +8,10 @@
 //
 // Reliable updates (mixed precision): the inner recurrence runs until its
 // residual norm has dropped by delta relative to the largest one since the last
-// update, or below the target; the system is then parked (RU_PENDING) until the
-// host has the FP64 true residual b - A x recomputed, which either finishes the
-// system or resumes it from the true residual.
+// update, or below the target; the system is then parked (RU_PENDING) until the FP64
+// true residual b - A x is recomputed (launched when the host sees the flag, or queued
+// behind every run of iterations), which either finishes the system or resumes it from
+// the true residual.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -74,7 +75,9 @@ struct ShiftStep {
 };
 
 struct Ctl {
-    int n_running;   // systems with SYS_RUNNING set; kernels of the inner loop exit when 0
+    int n_running;   // systems with SYS_RUNNING set: the gate of the classic fused single-field
+                     // kernels and of the batch's hops and finalize (the others gate on
+                     // their systems' flags)
     int pad0_;
     int nshift;      // multi-shift: shifts per RHS
     int nrhs;        // multi-shift: right-hand sides

@@ -726,8 +726,9 @@ __device__ __forceinline__ double det(const herm3 &q) {
 // the derivatives: about 90 (300 with the derivatives) in all, where the trigonometric
 // closed form takes several times that and the series in 3x3 matrices, as the derivative
 // had it before, 55 matrix products.  With c1 <= 3/4 the eigenvalues stay below 1 in
-// magnitude, the last of the 22 terms is below 1e-20 and no term cancels by more than a
-// factor e.  Larger Q: the triple of exp(iQ/2^s), squared s times in the same ring.
+// magnitude, what the first term left out (n = 22) would add is below 4e-22 in the f_j and
+// 4e-21 in their derivatives (1/22! is 8.9e-22), and no term cancels by more than a factor
+// e.  Larger Q: the triple of exp(iQ/2^s), squared s times in the same ring.
 struct ExpCoef {
     cpx<double> f[3], d0[3], d1[3];
 };
@@ -935,7 +936,7 @@ __device__ __forceinline__ cpx<double> trace_mul(const su3<double> &a, const su3
 // and the part Tr(E)/3 of E along the identity adds i Tr(E)/3 exp(iQ) in place of its
 // share in the terms above.  Multiples of the identity drop out of G.  (Before, L came
 // from a 14-term series of 3x3 products scaled and squared back: 55 products per link of
-// 75; the pass took 1399 us at 24^3 x 48, now 550.)
+// 75; the pass took 1209 us at 24^3 x 48 and 1752 at 32^4, now 518 and 712.)
 template <int FMT>
 __global__ __launch_bounds__(kStoutBlock) void stout_back1_kernel(StoutBackArgs a) {
     const Geom &g = a.geom;
@@ -1057,9 +1058,10 @@ __global__ __launch_bounds__(kStoutBlock) void stout_back1_kernel(StoutBackArgs 
 //   V1^dag [ V2^dag (H1 - H3) + H5 V2^dag ] V3:
 // 10 matrix products and 60 16-byte loads of the 12-real links and the G per direction
 // (12 and 126 when the six products were taken one by one from stored U^dag G), which is
-// what bounds the pass: both passes together 2107 -> 1213 us at 24^3
-// x 48, and 1114 with every matrix fetched a product ahead, at two waves per SIMD (three, in
-// 168 registers, spill: 1193).
+// what bounds the pass: 1050 -> 699 us at 24^3 x 48 and 1449 -> 994 at 32^4, with every
+// matrix fetched a product ahead, at two waves per SIMD.  (Both passes of 24^3 x 48 back to
+// back: 1213 before the fetches ahead, 1114 with them, 1193 at three waves, which spill in
+// 168 registers.)
 template <int FMT>
 __global__ __launch_bounds__(2 * kStapleLinks) void stout_back2_kernel(StoutBackArgs a) {
     // two waves over the same kStapleLinks links: wave 0 sums the +b sides, wave 1 the -b

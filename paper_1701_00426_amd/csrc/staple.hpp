@@ -66,8 +66,8 @@ struct LinkUpdateArgs {
 int launch_link_update(const LinkUpdateArgs &a, int fmt, hipStream_t stream);
 
 // The force through one stout step (staple.hip), in two passes over the links:
-// pass 1 writes Sigma' exp(iQ) + C^dag G^dag to out and U^dag G to ws; pass 2 adds
-// rho times the gathered products of ws with the links of the 3-link paths.
+// pass 1 writes Sigma' exp(iQ) + C^dag G^dag to out and G to ws; pass 2 adds rho times
+// the products of the neighbouring links' G with the links of the 3-link paths.
 struct StoutBackArgs {
     Geom geom;
     PencilTile tile;
