@@ -313,7 +313,8 @@ def multishift_stage_bytes(dims, stats, elem, slots=8):
     link_bytes = 8 * 6 * elem                      # FP32-12: 48 B per link, 8 per site
     hops = vh * (2 * launches * link_bytes + sum(base) * (2 * vec + 3 * vec))
     r_update = vh * sum(base) * 3 * vec            # r, q read, the next r written
-    p_update = vh * sum(base) * 3 * vec            # base p: r, p read, p written
+    # base p: r, p read, p written (after a full ring inside the shift update's launch)
+    p_update = vh * sum(base) * 3 * vec
     # each (shift, RHS) of a ring: p_k, x_k read and written; the ring's residuals are
     # re-read by every shift's blocks from L2: counted once
     rings = sum(-(-stats[k][j]["ms_iters"] // slots) for k in range(nshift) for j in range(nrhs))
