@@ -192,8 +192,7 @@ const char *stg_last_error(void);
  *     launches.  Automatic, when STG_TUNE_THREADS_PER_SITE is automatic too: launches
  *     of 8 fields take F = 1 up to Vh = 16384 with FP64-12 links and up to Vh = 65536 with
  *     FP32-12 / BF16-12 links, F = 2 above; launches of 4 fields take F = 1 above Vh = 16384
- *     with FP64-12 links and from Vh = 8192 up to 65536 with FP32-12 / BF16-12 links; other
- *     launches keep the threads per site.  It changes the order of
+ *     with FP64-12 links; other launches keep the threads per site.  It changes the order of
  *     additions, so results may differ in the last bits.
  *   STG_TUNE_CG_FORM: 0 (default: automatic: form 2 for a solve of one field, else
  *     form 1), 1 or 2: the form of

@@ -104,6 +104,7 @@ template <typename T, int FMT, bool STDPH, int NR, int FPG, int EPI>
 __global__ __launch_bounds__(64 * (NR / FPG)) void hop_fsplit_kernel(HopArgs a) {
     constexpr int G = NR / FPG;
     constexpr int W = LinkWords<T, FMT>::W;
+    constexpr bool kOwnSums = NR == 4;
     static_assert(NR % FPG == 0, "fields per wave must divide the fields of the launch");
     static_assert(fsplit_lds_bytes<T, FMT>() <= kSplitLdsMax, "link tile exceeds the LDS budget");
     if (gate_closed<NR>(a.state, a.gate_mask)) return;
@@ -156,6 +157,11 @@ __global__ __launch_bounds__(64 * (NR / FPG)) void hop_fsplit_kernel(HopArgs a) 
         // at run time
 #pragma unroll 1
         for (int d = 0; d < 4; ++d) {
+            // 4 fields: each direction summed by itself and added in order, as the direction
+            // split does it (comment at default_fields_per_wave)
+            vec3<T> own[FPG];
+            if constexpr (kOwnSums) zero_acc<T, FPG>(own);
+            vec3<T>(&sum)[FPG] = kOwnSums ? own : acc;
             uint32_t hf, hb;
             T pf, pb;
             dir_sites_rt<T, STDPH>(d, g, s, h, P, a.phases, hf, hb, pf, pb);
@@ -173,7 +179,7 @@ __global__ __launch_bounds__(64 * (NR / FPG)) void hop_fsplit_kernel(HopArgs a) 
                     const Pr w = *reinterpret_cast<const Pr *>(fb[jj][c] + of);
                     v.c[c] = {w.x, w.y};
                 }
-                acc_mv(acc[jj], pf, uf, v);
+                acc_mv(sum[jj], pf, uf, v);
             }
 #pragma unroll
             for (int k = 0; k < W; ++k) w[k] = tile[2 * d + 1][k][l];
@@ -188,7 +194,16 @@ __global__ __launch_bounds__(64 * (NR / FPG)) void hop_fsplit_kernel(HopArgs a) 
                     const Pr w = *reinterpret_cast<const Pr *>(fb[jj][c] + ob);
                     v.c[c] = {w.x, w.y};
                 }
-                acc_mdv(acc[jj], -pb, ub, v);
+                acc_mdv(sum[jj], -pb, ub, v);
+            }
+            if constexpr (kOwnSums) {
+#pragma unroll
+                for (int jj = 0; jj < FPG; ++jj)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        acc[jj].c[c].re += own[jj].c[c].re;
+                        acc[jj].c[c].im += own[jj].c[c].im;
+                    }
             }
         }
     }

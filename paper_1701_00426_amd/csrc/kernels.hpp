@@ -188,12 +188,15 @@ int launch_hop_fsplit(const HopArgs &a, int fmt, int nr, int epi, hipStream_t st
 //     1 up to Vh = 65536, for the same reason (16^3 x 32
 //     FP32-12 13.3 / 28.4 against 14.7 / 30.5, 8^4 9.1 against 11.0; 20^4 39.3 and 39.2).
 // 4 fields:
-//   FP64-12: 1 above Vh = 16384 (24^3 x 48 76.8 / 163 against 85.0 / 179 with 4 threads
-//     per site, 16^3 x 12 7.7 / 17.7 and 8.4 / 18.0; 12^4 6.2 / 12.1 and 6.4 / 11.6, with
-//     stored phases 6.5 / 12.7 and 6.6 / 11.7; 8^4 6.2 / 10.9 and 6.3 / 10.5);
-//   FP32-12, BF16-12: 1 from Vh = 8192 up to 65536 (16^3 x 32 19.5 against 20.6 and 16.7
-//     against 18.1, 16^3 x 8 10.1 and 10.6; 8^3 x 16 9.9 and 9.3; 20^4 27.0 and 25.6, 23.9 and
-//     23.4).
+//   FP64-12: 1 above Vh = 16384 (24^3 x 48 78.1 / 166 against 87.5 / 181 with 4 threads per
+//     site, 20^4 21.7 / 46.1 and 23.0 / 48.6, 16^4 8.5 / 20.1 and 8.6 / 19.7; 12^4 5.6 / 11.9
+//     and 5.7 / 11.2, with stored phases 6.1 / 12.4 and 6.5 / 11.7; 8^4 6.2 / 10.9 and 6.3 /
+//     10.5), each direction summed by itself and the four added in the order of the
+//     direction split, so that the results are its results: one chain of all eight
+//     products is off from 64 bits by 5 % more (1.82e-16 against 1.75e-16), for 1 % less time;
+//   FP32-12, BF16-12: none.  The split's chain over the decoded links is off by 1.27e-7
+//     where the direction split is by 7.1e-8, and it was 2 to 7 % faster at Vh 16384 to
+//     65536 only.  (8 fields took that chain at every size before the lines above.)
 constexpr uint32_t kFieldSplitSmallVh = 65536;
 constexpr uint32_t kFieldSplitRoundVh = 16384;  // 64-site blocks of 256 CUs
 
@@ -202,8 +205,7 @@ inline int default_fields_per_wave(int fmt, int nr, uint32_t Vh) {
     const bool one_round = Vh <= kFieldSplitRoundVh;
     if (fmt == FMT_C128_12) return nr == 8 ? (one_round ? 1 : 2) : (nr == 4 && !one_round) ? 1 : 0;
     if (fmt != FMT_C64_12 && fmt != FMT_BF16_12) return 0;
-    if (nr == 8) return small ? 1 : 2;
-    return (nr == 4 && small && Vh >= 8192) ? 1 : 0;
+    return nr == 8 ? (small ? 1 : 2) : 0;
 }
 
 // Whether such an automatic launch takes the layer order with 4 x3 planes per group when
