@@ -17,13 +17,13 @@
 // neighbourhood is mostly in the XCD's L2.  Neighbour half indices come from
 // coordinate arithmetic (no index tables).  The 8 paths of each side (above /
 // below the link) share their factors:
-//   above:  A = U_nu(x+mu), B = U_mu(x+nu)^dag, C = U_nu(x)^dag,
+//   above:  A = U_nu(x+mu), B = U_mu(x+nu)^dag, C = U_nu(x)^dag, X = A B,
 //           Y = A U_nu(x+mu+nu) U_mu(x+2nu)^dag U_nu(x+nu)^dag,
-//           Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag,
-//           W = A B U_mu(x-mu+nu)^dag U_nu(x-mu)^dag,
-//   1x1: A B C;  1x2: Y C (long side along nu), Z B C (long side forward), W U_mu(x-mu)
-//   (long side backward), so the side contributes
-//           [c1 Y + (c1 Z + c0 A) B] C + c1 W U_mu(x-mu),
+//           Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag B,
+//           W = X U_mu(x-mu+nu)^dag U_nu(x-mu)^dag,
+//   1x1: X C;  1x2: Y C (long side along nu), Z C (long side forward), W U_mu(x-mu) (long
+//   side backward), so the side contributes
+//           [c0 X + c1 (Y + Z)] C + c1 W U_mu(x-mu),
 // 11 SU(3) products instead of 14 taken path by path; below the link likewise
 // with nu -> -nu.  Products accumulate in the arithmetic type of the format
 // (FP64 for complex128 links, FP32 for the 12-real FP32 / BF16 ones).
@@ -189,6 +189,18 @@ __device__ __forceinline__ void axpby(su3<T> &c, T s, T r, const su3<T> &b) {
         for (int j = 0; j < 3; ++j) {
             c.e[i][j].re = fmat(s, c.e[i][j].re, r * b.e[i][j].re);
             c.e[i][j].im = fmat(s, c.e[i][j].im, r * b.e[i][j].im);
+        }
+}
+
+// C += s B
+template <typename T>
+__device__ __forceinline__ void axpy(su3<T> &c, T s, const su3<T> &b) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            c.e[i][j].re = fmat(s, b.e[i][j].re, c.e[i][j].re);
+            c.e[i][j].im = fmat(s, b.e[i][j].im, c.e[i][j].im);
         }
 }
 
@@ -418,8 +430,8 @@ __device__ __forceinline__ su3<T> dagger(const su3<T> &u) {
 }
 
 // The four paths on one side of the link (header; UP: the +nu side, else the -nu side, every
-// U_nu step reversed): acc += [c1 Y + (c1 Z + c0 A) U_mu(x+nu)^dag] C, and the path whose long
-// side runs backward, W U_mu(x-mu): with BACK its last factor, common to all sides, is left to
+// U_nu step reversed): acc += [c0 X + c1 (Y + Z)] C, and the path whose long side
+// runs backward, W U_mu(x-mu): with BACK its last factor, common to all sides, is left to
 // the caller and W added to back, else c1 times the path is added to acc.  Every link is
 // fetched one product or more before the one that uses it; u0 holds U_mu(x+mu) on entry
 // and is fetched again for the next side.
@@ -428,11 +440,14 @@ __device__ __forceinline__ su3<T> dagger(const su3<T> &u) {
 // SU(3) (FP64-12 at 32^4 1490 us, FP32-12 752), but the links of a trajectory leave it: each
 // update rounds their rows, and a product completed that way is off by their departure.
 // Against 64-bit sums of the stored links, 8^3 x 16 in FP32-12 after 0 / 10 / 100 / 1000
-// updates: 1.2e-7 / 2.3e-7 / 6.9e-7 / 7.7e-6 with two rows, 1.3e-7 at any number with three.
+// updates: 1.2e-7 / 2.3e-7 / 6.9e-7 / 7.7e-6 with two rows, 1.1e-7 at any number with three.
 // 32^4 with every link fetched where it is used (11 products, FP64-12 on two threads) / so:
-// FP64-12 1929 / 1707 us, FP32-12 1068 / 857, BF16-12 880 / 791.  In FP64 the matrices take
-// 310 registers and one wave runs per SIMD; held to two, it spills 248 B per lane (2500 us),
+// FP64-12 1929 / 1703 us, FP32-12 1068 / 847, BF16-12 880 / 785.  In FP64 the matrices take
+// 300 registers and one wave runs per SIMD; held to two, it spills 248 B per lane (2500 us),
 // and with a matrix fetched twice and the last factor of every side multiplied 60 B (1815).
+// The terms of the sums are products of their own, scaled and added afterwards: chained into
+// the sum, each of their nine entries rounds three times at the sum's size (BF16-12 1.24e-7
+// against 1.01e-7).
 // mp1 .. n2: lexicographic displacements of x +- mu, x + 2mu, x +- nu, x +- 2nu (periodic).
 template <typename T, int FMT, bool BACK, bool UP>
 __device__ __forceinline__ void side(su3<T> &acc, su3<T> &back, RawLink<T, FMT> &u0,
@@ -445,7 +460,7 @@ __device__ __forceinline__ void side(su3<T> &acc, su3<T> &back, RawLink<T, FMT> 
         return UP ? mmd(a, b) : mm(a, b);
     };
     RawLink<T, FMT> p, q;
-    // Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag
+    // Z = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag B, B = U_mu(x+nu)^dag
     U.fetch(p, nu, UP ? mp2 : mp2 + n1, UP ? 0 : 1);
     U.fetch(q, mu, mp1 + n1, 0);
     fetched();
@@ -470,15 +485,16 @@ __device__ __forceinline__ void side(su3<T> &acc, su3<T> &back, RawLink<T, FMT> 
     su3<T> x;
     {
         const su3<T> b = p.link();
-        axpby(z, c1, c0, a);
-        mmd_acc(g, z, b);
+        z = mmd(z, b);
+        axpy(g, c1, z);
         U.fetch(q, mu, mm1 + n1, 0);
         fetched();
-        x = mmd(a, b);
+        x = mmd(a, b);  // X = A B
     }
-    // W = A U_mu(x+nu)^dag U_mu(x-mu+nu)^dag U_nu(x-mu)^dag
     U.fetch(p, nu, UP ? mm1 : mm1 + n1, UP ? 1 : 0);
     fetched();
+    axpy(g, c0, x);
+    // W = X U_mu(x-mu+nu)^dag U_nu(x-mu)^dag
     x = mmd(x, q.link());
     if constexpr (!BACK) {
         U.fetch(q, mu, mm1, 1);
@@ -486,8 +502,7 @@ __device__ __forceinline__ void side(su3<T> &acc, su3<T> &back, RawLink<T, FMT> 
         x = muld(x, p.link());
         U.fetch(p, nu, UP ? 0 : n1, UP ? 0 : 1);
         fetched();
-        scale(x, c1);
-        mm_acc(acc, x, q.link());
+        axpy(acc, c1, mm(x, q.link()));
     } else {
         U.fetch(q, nu, UP ? 0 : n1, UP ? 0 : 1);
         fetched();
@@ -615,10 +630,7 @@ void staple_kernel(StapleArgs a) {
                                                c0, c1);
             }
         }
-        if constexpr (kBack) {
-            scale(back, c1);
-            mm_acc(acc, back, U(mu, mm1, 1));
-        }
+        if constexpr (kBack) axpy(acc, c1, mm(back, U(mu, mm1, 1)));
     }
     if (TPL == 2) {
         if (q == 1) {
