@@ -870,8 +870,10 @@ __device__ __forceinline__ su3<double> exp_matrix(const ExpCoef &c, const herm3 
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             if (i == k) {
-                e.e[i][k] = {fmat(c.f[2].re, b.e[i][k].re, fmat(c.f[1].re, a.e[i][k].re, c.f[0].re)),
-                             fmat(c.f[2].im, b.e[i][k].re, fmat(c.f[1].im, a.e[i][k].re, c.f[0].im))};
+                // the largest term last (f0 of the real part, f1 Q of the imaginary one), so that
+                // one addition rounds at its size
+                e.e[i][k] = {c.f[0].re + fmat(c.f[2].re, b.e[i][k].re, c.f[1].re * a.e[i][k].re),
+                             fmat(c.f[1].im, a.e[i][k].re, fmat(c.f[2].im, b.e[i][k].re, c.f[0].im))};
             } else {
                 cpx<double> v = cmul(c.f[1], a.e[i][k]);
                 cfma(v, c.f[2], b.e[i][k]);
