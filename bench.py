@@ -642,8 +642,8 @@ def bench_force(profile=False, applies=50):
 
 # One stout-smearing step per link: 12 SU(3) products for the six 3-link paths
 # (2484 flop), Omega (198), Q^2 and Tr Q^3 (261), exp(iQ) = f0 + f1 Q + f2 Q^2 (189)
-# and exp(iQ) U (198), plus the weighting: about 3375 flop (trigonometric functions
-# and the row-2 reconstruction of FP64-12 links not counted).
+# and exp(iQ) U (198), plus the weighting: about 3375 flop (the coefficients
+# f_j and the row-2 reconstruction of FP64-12 links not counted).
 STOUT_FLOPS_PER_LINK = 3375
 
 
